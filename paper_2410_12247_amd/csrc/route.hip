@@ -2,177 +2,27 @@
 //
 // Logits (the topKGating operator): every logit is ONE fp32 fma chain over
 // h in ascending order, started from +0, with the bias added once at the
-// end -- the same bits as a sequential fma loop on the CPU.  A thread keeps
-// a 4-token x TE-expert block of chains in registers; x and the router are
-// staged through LDS 32 h at a time.
-//
-// Selection: the token's logits are spread over a wave (lane l holds experts
-// l, l+64, l+128, l+192); each of the k rounds is a wave-wide max of 64-bit
-// keys (order-preserving logit bits << 32 | inverted expert index, so ties
-// go to the lower index) built from DPP row permutes and readlane.  The
-// winner's lane clears its key.  Softmax weights are computed in fp64 and
-// rounded to fp32 once; the full-softmax denominator is a DPP wave sum.
+// end -- the same bits as a sequential fma loop on the CPU, from every
+// kernel: the matrix-core one (route_mfma.hip), the chain-per-lane one for a
+// few tokens of at most 16 experts, and, for operands that are not 16-byte
+// aligned, the lane-per-token and register-tiled ones.
 #include "common.h"
 
 #include <type_traits>
 
+#include "route_common.h"
 #include "route_lane_asm.h"
 
 namespace moe {
 namespace {
 
-typedef __attribute__((address_space(3))) void lds_void_t;
-typedef __attribute__((address_space(1))) void gbl_void_t;
-
 constexpr int RT_THREADS = 256;
 
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp32(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xF, 0xF, false);
-}
-
-__device__ __forceinline__ uint64_t max_u64(uint64_t a, uint64_t b) { return a > b ? a : b; }
-
-template <int CTRL>
-__device__ __forceinline__ uint64_t dpp64(uint64_t v) {
-    uint32_t lo = dpp32<CTRL>((uint32_t)v);
-    uint32_t hi = dpp32<CTRL>((uint32_t)(v >> 32));
-    return ((uint64_t)hi << 32) | lo;
-}
-
-__device__ __forceinline__ uint64_t readlane64(uint64_t v, int l) {
-    uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
-    uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), l);
-    return ((uint64_t)hi << 32) | lo;
-}
-
-// Wave-wide max: butterfly inside each 16-lane row (quad_perm 1032, quad_perm
-// 2301, half-row mirror, row mirror), then the four row results by readlane.
-__device__ __forceinline__ uint64_t wave_max_u64(uint64_t k) {
-    k = max_u64(k, dpp64<0xB1>(k));
-    k = max_u64(k, dpp64<0x4E>(k));
-    k = max_u64(k, dpp64<0x141>(k));
-    k = max_u64(k, dpp64<0x140>(k));
-    return max_u64(max_u64(readlane64(k, 0), readlane64(k, 16)),
-                   max_u64(readlane64(k, 32), readlane64(k, 48)));
-}
-
-__device__ __forceinline__ double dpp_f64(double v, int which) {
-    uint64_t b = __builtin_bit_cast(uint64_t, v);
-    uint64_t r;
-    switch (which) {
-        case 0: r = dpp64<0xB1>(b); break;
-        case 1: r = dpp64<0x4E>(b); break;
-        case 2: r = dpp64<0x141>(b); break;
-        default: r = dpp64<0x140>(b); break;
-    }
-    return __builtin_bit_cast(double, r);
-}
-
-// Wave-wide fp64 sum; every lane combines the same pairs (commutative adds),
-// so the result is identical in all lanes and from run to run.
-__device__ __forceinline__ double wave_sum_f64(double v) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) v = v + dpp_f64(v, i);
-    uint64_t b = __builtin_bit_cast(uint64_t, v);
-    double r0 = __builtin_bit_cast(double, readlane64(b, 0));
-    double r1 = __builtin_bit_cast(double, readlane64(b, 16));
-    double r2 = __builtin_bit_cast(double, readlane64(b, 32));
-    double r3 = __builtin_bit_cast(double, readlane64(b, 48));
-    return (r0 + r1) + (r2 + r3);
-}
-
-__device__ __forceinline__ uint64_t logit_key(float z, int e) {
-    uint32_t u = __float_as_uint(z);
-    if (u == 0x80000000u) u = 0;  // -0 ranks equal to +0
-    const uint32_t ord = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-    return ((uint64_t)ord << 32) | (uint32_t)(0xFFFFFFFFu - (uint32_t)e);
-}
-
-__device__ __forceinline__ float key_logit(uint64_t key) {
-    const uint32_t ord = (uint32_t)(key >> 32);
-    const uint32_t u = (ord & 0x80000000u) ? (ord & 0x7FFFFFFFu) : ~ord;
-    return __uint_as_float(u);
-}
-
-__device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
-__device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
-
-// Top-k and softmax weights of token t from its E logits (zrow, in LDS),
-// by one wave: lane l holds experts l, l+64, l+128, l+192; each of the k
-// rounds takes the wave-wide max key; the weights are fp64 softmax values
-// rounded once to fp32.
-__device__ __forceinline__ void select_token(const float *zrow, int64_t t, int E, int k,
-                                             int renorm, int lane, int32_t *__restrict__ ids,
-                                             float *__restrict__ wout) {
-    uint64_t key[4];
-    float zl[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int e = lane + 64 * q;
-        zl[q] = e < E ? zrow[e] : 0.0f;
-        key[q] = e < E ? logit_key(zl[q], e) : 0ull;
-    }
-    int sel_e[kMaxTopK];
-    float sel_z[kMaxTopK];
-#pragma unroll
-    for (int j = 0; j < kMaxTopK; ++j) {
-        sel_e[j] = 0;
-        sel_z[j] = 0.0f;
-        if (j < k) {
-            const uint64_t best =
-                wave_max_u64(max_u64(max_u64(key[0], key[1]), max_u64(key[2], key[3])));
-            sel_e[j] = (int)(0xFFFFFFFFu - (uint32_t)best);
-            sel_z[j] = key_logit(best);
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (key[q] == best) key[q] = 0ull;
-        }
-    }
-    const double zmax = (double)sel_z[0];
-    double denom;
-    if (renorm) {
-        denom = 0.0;
-#pragma unroll
-        for (int j = 0; j < kMaxTopK; ++j)
-            if (j < k) denom += exp((double)sel_z[j] - zmax);
-    } else {
-        double part = 0.0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            if (lane + 64 * q < E) part += exp((double)zl[q] - zmax);
-        denom = wave_sum_f64(part);
-    }
-#pragma unroll
-    for (int j = 0; j < kMaxTopK; ++j) {
-        if (j < k && lane == j) {
-            ids[t * k + j] = sel_e[j];
-            wout[t * k + j] = (float)(exp((double)sel_z[j] - zmax) / denom);
-        }
-    }
-}
-
-// One 16-byte-per-lane LDS-DMA request (lane l's bytes land at lds_addr +
-// 16 l; lds_addr must be the same in every lane), written out so that the
-// compiler does not see an LDS write in
-// flight: it would put a full vmcnt(0) in front of every later LDS read,
-// which makes the next chunk's loads finish before the current chunk is
-// multiplied.  The kernel's own vmcnt wait and barrier order the data.
-__device__ __forceinline__ void dma16_to_lds(const void *gptr, uint32_t lds_addr) {
-    // the LDS address goes in through an "{m0}" operand, so the compiler
-    // itself writes m0 (and knows it does); the s_nop separates that write
-    // from the load that reads it
-    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-                 :
-                 : "v"(gptr), "{m0}"(__builtin_amdgcn_readfirstlane(lds_addr))
-                 : "memory");
-}
-
-// Register-tiled router for more than 16 experts.
+// Register-tiled router for more than 16 experts (operands of any
+// alignment).
 //
 // Logits phase layout: 256 threads = TG token groups x EG expert groups
-// (EG = 16, or 32 for 129 to 160 experts); a thread
-// owns TT tokens (tg + TG i: consecutive lanes read rows 36 floats apart, so
+// (EG = 16); a thread owns TT tokens (tg + TG i: consecutive lanes read rows 36 floats apart, so
 // eight lanes of a 16-byte LDS read land on distinct banks) x TE experts
 // (TE = ceil(E / EG)) and keeps their fma chains in registers.  x and the
 // router are staged through two LDS buffers HC h at a time: the router rows
@@ -329,20 +179,8 @@ __global__ __launch_bounds__(RT_THREADS) void route_kernel(const bf16_t *__restr
     }
 }
 
-// Top-k of logits z [T][E] (any E): one wave per token.
-__global__ __launch_bounds__(RT_THREADS) void route_select_kernel(const float *__restrict__ z,
-                                                                  int64_t T, int E, int k,
-                                                                  int renorm,
-                                                                  int32_t *__restrict__ ids,
-                                                                  float *__restrict__ wout) {
-    const int64_t t = (int64_t)blockIdx.x * (RT_THREADS / 64) + (threadIdx.x >> 6);
-    if (t >= T) return;
-    select_token(z + t * E, t, E, k, renorm, threadIdx.x & 63, ids, wout);
-}
-
-// Lane-per-token router (E <= 16; and blocks of 16 experts for more experts
-// and few tokens).  Lane l of a wave owns the chains of
-// token l % TPW for R * G experts (the wave's 64 lanes are R sets of TPW =
+// Lane-per-token router (E <= 16, operands of any alignment).  Lane l of a
+// wave owns the chains of token l % TPW for R * G experts (the wave's 64 lanes are R sets of TPW =
 // 64 / R tokens; set s takes G experts of its own): x is the lane's own
 // operand, and the router element of each fma comes from a register that
 // holds 16 consecutive h in each 16-lane row, broadcast by DPP (see
@@ -361,12 +199,7 @@ __global__ __launch_bounds__(RT_THREADS) void route_select_kernel(const float *_
 // themselves left it behind their VALU stream: measured on the Mixtral shape
 // (16384 tokens, H = 4096, 8 experts), 41 us that way against 36 us with the
 // producer wave.  The logits then go to LDS and one lane per token takes the
-// top-k and the softmax weights; in the expert-block form (ZOUT) they go to
-// a [T][E] buffer for route_select_kernel.  For more than 16 experts the
-// chain per lane is as long as for 16 (H fmas), so up to a few thousand
-// tokens this beats the register-tiled kernel, whose workgroups each run
-// 5 to 20 chains per thread (E = 160, measured in the forward: 64 tokens
-// 65 -> 50 us, 1024 tokens 115 -> 81, 4096 tokens 261 -> 204).
+// top-k and the softmax weights.
 constexpr int RL_HS = 64;     // h per stage
 constexpr int RL_NS_MAX = 6;  // ring stages at most (deeper rings measured no faster)
 
@@ -378,15 +211,6 @@ constexpr int lane_ring(int stage, int per) {
     int n = RL_NS_MAX;
     while (n > 2 && (n * stage > 80 * 1024 || (n - 1) * per > 63)) n -= 2;
     return n;
-}
-
-// Calls f(integral_constant<int, I>) for I = B .. N - 1.
-template <int B, int N, class F>
-__device__ __forceinline__ void lane_unroll(F &&f) {
-    if constexpr (B < N) {
-        f(std::integral_constant<int, B>{});
-        lane_unroll<B + 1, N>(f);
-    }
 }
 
 template <int G>
@@ -469,55 +293,6 @@ __device__ __forceinline__ void lane_wait_vm(int n) {
     lane_wait_vm_k<PER, NS - 1>(n);
 }
 
-// top-k and softmax weights of one token from its E logits, by one lane
-template <int EP>
-__device__ __forceinline__ void select_lane(const float *zrow, int64_t t, int E, int k,
-                                            int renorm, int32_t *__restrict__ ids,
-                                            float *__restrict__ wout) {
-    uint64_t key[EP];
-    float z[EP];
-#pragma unroll
-    for (int e = 0; e < EP; ++e) {
-        z[e] = e < E ? zrow[e] : 0.0f;
-        key[e] = e < E ? logit_key(z[e], e) : 0ull;
-    }
-    int sel_e[kMaxTopK];
-    float sel_z[kMaxTopK];
-#pragma unroll
-    for (int j = 0; j < kMaxTopK; ++j) {
-        sel_e[j] = 0;
-        sel_z[j] = 0.0f;
-        if (j < k) {
-            uint64_t best = key[0];
-#pragma unroll
-            for (int e = 1; e < EP; ++e) best = max_u64(best, key[e]);
-            sel_e[j] = (int)(0xFFFFFFFFu - (uint32_t)best);
-            sel_z[j] = key_logit(best);
-#pragma unroll
-            for (int e = 0; e < EP; ++e)
-                if (key[e] == best) key[e] = 0ull;
-        }
-    }
-    const double zmax = (double)sel_z[0];
-    double denom = 0.0;
-    if (renorm) {
-#pragma unroll
-        for (int j = 0; j < kMaxTopK; ++j)
-            if (j < k) denom += exp((double)sel_z[j] - zmax);
-    } else {
-#pragma unroll
-        for (int e = 0; e < EP; ++e)
-            if (e < E) denom += exp((double)z[e] - zmax);
-    }
-#pragma unroll
-    for (int j = 0; j < kMaxTopK; ++j) {
-        if (j < k) {
-            ids[t * k + j] = sel_e[j];
-            wout[t * k + j] = (float)(exp((double)sel_z[j] - zmax) / denom);
-        }
-    }
-}
-
 // select_lane's result for one token of E <= 16 logits (zrow, in LDS), by
 // the whole wave: lane e holds expert e's key, so each of the k rounds is a
 // wave-wide max (the same winners in the same order), and each lane takes
@@ -568,18 +343,14 @@ __device__ __forceinline__ void select_wave16(const float *zrow, int64_t t, int 
     }
 }
 
-// ZOUT: the workgroup takes experts blockIdx.y * EP .. (any E) and writes
-// its logits (bias added) to zout [T][E] for a selection kernel; else one
-// workgroup holds every expert (E <= EP) and selects in place.
-template <int G, int R, int NW, int NS, bool ZOUT>
+template <int G, int R, int NW, int NS>
 __global__ __launch_bounds__(64 * NW + 64) void route_lane_kernel(const bf16_t *__restrict__ x,
                                                              const float *__restrict__ wr,
                                                              const float *__restrict__ bias,
                                                              int64_t T, int H, int E, int k,
                                                              int renorm,
                                                              int32_t *__restrict__ ids,
-                                                             float *__restrict__ wout,
-                                                             float *__restrict__ zout) {
+                                                             float *__restrict__ wout) {
     constexpr int TPW = 64 / R;              // tokens per wave (and per workgroup)
     constexpr int EP = NW * R * G;           // experts per workgroup
     constexpr int XB = TPW * RL_HS * 2;      // bytes of a stage's x rows
@@ -604,7 +375,6 @@ __global__ __launch_bounds__(64 * NW + 64) void route_lane_kernel(const bf16_t *
     const int tl = lane % TPW;                   // token of this lane
     const int eb = (wave * R + lane / TPW) * G;  // its first expert in the block
     const int64_t t0 = (int64_t)blockIdx.x * TPW;
-    const int e0 = ZOUT ? (int)blockIdx.y * EP : 0;  // the block's first expert
 
     // the producer's DMA requests q of a stage: q < NXR: 8 x rows of 128
     // bytes (lane i: row 8 q + i / 8, 16-byte chunk (i % 8) ^ lane_swz(row)
@@ -623,7 +393,7 @@ __global__ __launch_bounds__(64 * NW + 64) void route_lane_kernel(const bf16_t *
             step_bytes[q] = RL_HS * 2;
         } else {
             const int qw = q - NXR;
-            const int e = min(e0 + qw * 4 + (lane >> 4), E - 1);  // rows past E: unused copies
+            const int e = min(qw * 4 + (lane >> 4), E - 1);  // rows past E: unused copies
             src[q] = reinterpret_cast<const char *>(wr + (int64_t)e * H) + (lane & 15) * 16;
             dst[q] = XB + qw * 1024;
             step_bytes[q] = RL_HS * 4;
@@ -685,17 +455,6 @@ __global__ __launch_bounds__(64 * NW + 64) void route_lane_kernel(const bf16_t *
         for (int st0 = 0; st0 < nst; st0 += NS)
             lane_unroll<0, NS>([&](auto u) { step(st0 + decltype(u)::value, u); });
     }
-    if constexpr (ZOUT) {
-        // (the producer's DMA has all been waited for: its last wait is vmcnt(0))
-        if (producer) return;
-        const int64_t t = t0 + tl;
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const int e = e0 + eb + g;
-            if (e < E && t < T) zout[t * E + e] = bias ? acc[g] + bias[e] : acc[g];
-        }
-        return;
-    }
     __syncthreads();  // no wave reads the ring any more; no DMA in flight
 
     // logits to LDS, zs[token][e] with an odd row stride
@@ -743,32 +502,13 @@ hipError_t launch_lane(const moe_dims &d, const bf16_t *x, const float *wr, cons
     constexpr int STAGE = TPW * RL_HS * 2 + NW * R * G * RL_HS * 4;
     constexpr int PER = STAGE / 1024;
     const int64_t blocks = (d.tokens + TPW - 1) / TPW;
-    route_lane_kernel<G, R, NW, lane_ring(STAGE, PER), false>
+    route_lane_kernel<G, R, NW, lane_ring(STAGE, PER)>
         <<<(unsigned)blocks, 64 * NW + 64, 0, s>>>(x, wr, bias, d.tokens, d.hidden, d.experts,
-                                                   d.top_k, d.renormalize, ids, w, nullptr);
+                                                   d.top_k, d.renormalize, ids, w);
     return hipGetLastError();
 }
 
-// Any number of experts in blocks of NW * R * G per workgroup, logits
-// through z [T][E], then the selection kernel (one wave per token).
-template <int G, int R, int NW>
-hipError_t launch_lane_z(const moe_dims &d, const bf16_t *x, const float *wr, const float *bias,
-                         int32_t *ids, float *w, float *z, hipStream_t s) {
-    constexpr int TPW = 64 / R, EP = NW * R * G;
-    constexpr int STAGE = TPW * RL_HS * 2 + EP * RL_HS * 4;
-    constexpr int PER = STAGE / 1024;
-    const dim3 grid((unsigned)((d.tokens + TPW - 1) / TPW), (unsigned)((d.experts + EP - 1) / EP));
-    route_lane_kernel<G, R, NW, lane_ring(STAGE, PER), true><<<grid, 64 * NW + 64, 0, s>>>(
-        x, wr, bias, d.tokens, d.hidden, d.experts, d.top_k, d.renormalize, ids, w, z);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    route_select_kernel<<<(unsigned)((d.tokens + 3) / 4), RT_THREADS, 0, s>>>(
-        z, d.tokens, d.experts, d.top_k, d.renormalize, ids, w);
-    return hipGetLastError();
-}
-
-// Few-token router: one wave per token and block of 4 NQ experts; lane l
-// runs the chain of expert e0 + l.  A chain is H dependent fmas whatever
+// Few-token router: one wave per token; lane l runs the chain of expert l.  A chain is H dependent fmas whatever
 // the mapping, so at a few tokens (a SIMD for every wave) the chain's
 // latency is the router's time: a dependent fp32 fma issues every ~6
 // cycles when both operands are in vector registers (measured; ~9 when one
@@ -788,31 +528,9 @@ namespace chain {
 // dynamic LDS of the ring (NS * NQ KB) and the fp32 x row, at most 64 KB
 constexpr size_t kMaxLds = 65536;
 
-struct Half {  // 32 h: x (the same in every lane) and the lane's router row
-    floatx4 x[8], w[8];
-};
-
 // Ring slot layout: row r (lane r's expert) at 256 r, its 16-byte chunk c
 // at position c ^ (r % 16), so the 16 rows one read instruction touches
 // for a given chunk fall on distinct banks.
-template <int OFF>
-__device__ __forceinline__ void read(Half &hv, const char *lds, const int (&woff)[16], int half,
-                                     int xoff) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        hv.w[j] = *reinterpret_cast<const floatx4 *>(lds + OFF + woff[8 * half + j]);
-        hv.x[j] = *reinterpret_cast<const floatx4 *>(lds + xoff + 16 * j);
-    }
-}
-
-__device__ __forceinline__ float run(const Half &hv, float acc) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc = __builtin_fmaf(hv.x[j][c], hv.w[j][c], acc);
-    return acc;
-}
-
 // The DPP form: lane n of each 16-lane row holds x[4n .. 4n+3] of the 64-h
 // block (xq; every row reads the same 256 bytes, one read per block instead
 // of sixteen), and the fma for h = 4n + c takes component c broadcast from
@@ -913,26 +631,24 @@ __device__ __forceinline__ float run_dpp(const floatx4 &xq, const HalfW &hv, flo
 }  // namespace chain
 
 // NQ: router-row DMA requests per block (4 rows of 256 bytes each); NS ring
-// slots, NS - 2 blocks of requests in flight.  ZOUT: logits (bias added) to
-// zout [T][E] for route_select_kernel; else every expert is in the wave
+// slots, NS - 2 blocks of requests in flight; every expert is in the wave
 // (E <= 4 NQ) and it selects in place.  Dynamic LDS: NS * NQ KB of ring,
 // then the fp32 x row.
 // (the body is a device function: the host pass of a kernel template whose
 // own body calls generic lambdas over target builtins emits no launch stub)
-template <int NQ, int NS, bool ZOUT>
+template <int NQ, int NS>
 __device__ __forceinline__ void route_chain(char *lds, const bf16_t *__restrict__ x,
                                             const float *__restrict__ wr,
                                             const float *__restrict__ bias, int64_t T, int H,
                                             int E, int k, int renorm,
-                                            int32_t *__restrict__ ids, float *__restrict__ wout,
-                                            float *__restrict__ zout) {
+                                            int32_t *__restrict__ ids,
+                                            float *__restrict__ wout) {
     constexpr int SLOT = NQ * 1024;  // bytes: 4 NQ rows of 64 fp32
     constexpr int RING = NS * SLOT;
     static_assert(NS >= 3 && (NS - 2) * NQ <= 63 && RING <= 65536, "ring");
     const int64_t t = blockIdx.x;
     const int lane = threadIdx.x;
-    const int e0 = (int)blockIdx.y * 4 * NQ;
-    const int e = e0 + lane;
+    const int e = lane;
     const bool live = lane < 4 * NQ && e < E;
     const int nb = H / 64;
 
@@ -946,7 +662,7 @@ __device__ __forceinline__ void route_chain(char *lds, const bf16_t *__restrict_
     for (int q = 0; q < NQ; ++q) {
         const int r = 4 * q + lane / 16;
         const int c = (lane & 15) ^ (r & 15);
-        voff[q] = (uint32_t)(((int64_t)min(e0 + r, E - 1) * H + 4 * c) * 4);
+        voff[q] = (uint32_t)(((int64_t)min(r, E - 1) * H + 4 * c) * 4);
     }
     auto issue = [&](int blk, auto slot) {  // block blk (clamped) into a slot
         constexpr int S = decltype(slot)::value;
@@ -1020,65 +736,45 @@ __device__ __forceinline__ void route_chain(char *lds, const bf16_t *__restrict_
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the clamped tail requests
 
     const float z = bias && live ? acc + bias[e] : acc;
-    if constexpr (ZOUT) {
-        if (live) zout[t * E + e] = z;
-        return;
-    }
     float *zs = reinterpret_cast<float *>(lds);
     __syncthreads();  // every ring read done before the logits reuse it
     zs[lane] = z;
     __syncthreads();
-    if (E <= 16) {
-        select_wave16(zs, t, E, k, renorm, lane, ids, wout);
-    } else {
-        select_token(zs, t, E, k, renorm, lane, ids, wout);
-    }
+    select_wave16(zs, t, E, k, renorm, lane, ids, wout);
 }
 
-template <int NQ, int NS, bool ZOUT>
+template <int NQ, int NS>
 __global__ __launch_bounds__(64) void route_chain_kernel(const bf16_t *__restrict__ x,
                                                          const float *__restrict__ wr,
                                                          const float *__restrict__ bias,
                                                          int64_t T, int H, int E, int k,
                                                          int renorm, int32_t *__restrict__ ids,
-                                                         float *__restrict__ wout,
-                                                         float *__restrict__ zout) {
+                                                         float *__restrict__ wout) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    route_chain<NQ, NS, ZOUT>(lds, x, wr, bias, T, H, E, k, renorm, ids, wout, zout);
+    route_chain<NQ, NS>(lds, x, wr, bias, T, H, E, k, renorm, ids, wout);
 }
 
 template <int NQ, int NS>
 hipError_t launch_chain_q(const moe_dims &d, const bf16_t *x, const float *wr, const float *bias,
-                          int32_t *ids, float *w, float *z, hipStream_t s) {
-    const dim3 grid((unsigned)d.tokens, (unsigned)((d.experts + 4 * NQ - 1) / (4 * NQ)));
+                          int32_t *ids, float *w, hipStream_t s) {
     const size_t lds = (size_t)NS * NQ * 1024 + (size_t)d.hidden * 4;
-    if (d.experts <= 4 * NQ) {
-        route_chain_kernel<NQ, NS, false><<<grid, 64, lds, s>>>(
-            x, wr, bias, d.tokens, d.hidden, d.experts, d.top_k, d.renormalize, ids, w, nullptr);
-        return hipGetLastError();
-    }
-    route_chain_kernel<NQ, NS, true><<<grid, 64, lds, s>>>(
-        x, wr, bias, d.tokens, d.hidden, d.experts, d.top_k, d.renormalize, ids, w, z);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    route_select_kernel<<<(unsigned)((d.tokens + 3) / 4), RT_THREADS, 0, s>>>(
-        z, d.tokens, d.experts, d.top_k, d.renormalize, ids, w);
+    route_chain_kernel<NQ, NS><<<(unsigned)d.tokens, 64, lds, s>>>(
+        x, wr, bias, d.tokens, d.hidden, d.experts, d.top_k, d.renormalize, ids, w);
     return hipGetLastError();
 }
 
-// up to 8 experts: one wave of 8 chains; up to 16: one of 16; more: blocks
-// of 16 experts (a wave each) and the selection kernel
+// up to 8 experts: one wave of 8 chains per token; up to 16: one of 16
 constexpr int kChainSlots = 8;
 int chain_requests(const moe_dims &d) { return d.experts <= 8 ? 2 : 4; }
 bool chain_fits(const moe_dims &d) {
-    return (size_t)kChainSlots * chain_requests(d) * 1024 + (size_t)d.hidden * 4 <=
-           chain::kMaxLds;
+    return d.experts <= 16 && (size_t)kChainSlots * chain_requests(d) * 1024 +
+                                      (size_t)d.hidden * 4 <=
+                                  chain::kMaxLds;
 }
 hipError_t launch_chain(const moe_dims &d, const bf16_t *x, const float *wr, const float *bias,
-                        int32_t *ids, float *w, float *z, hipStream_t s) {
-    if (chain_requests(d) == 2)
-        return launch_chain_q<2, kChainSlots>(d, x, wr, bias, ids, w, z, s);
-    return launch_chain_q<4, kChainSlots>(d, x, wr, bias, ids, w, z, s);
+                        int32_t *ids, float *w, hipStream_t s) {
+    if (chain_requests(d) == 2) return launch_chain_q<2, kChainSlots>(d, x, wr, bias, ids, w, s);
+    return launch_chain_q<4, kChainSlots>(d, x, wr, bias, ids, w, s);
 }
 
 // Per-SIMD fma work of a lane-router shape: every wave issues (G + 1) VALU
@@ -1109,35 +805,22 @@ hipError_t launch_lane_router(const moe_dims &d, const bf16_t *x, const float *w
 hipError_t launch_route(const moe_dims &d, const bf16_t *x, const float *wr, const float *bias,
                         int32_t *ids, float *w, float *logits, hipStream_t s) {
     if (d.tokens <= 0) return hipSuccess;
-    // few tokens: the chain-per-lane kernel (its 16-byte loads of x need
-    // the rows 16-byte aligned; more than 16 experts need the logits buffer;
-    // measured against the lane kernels, Mixtral and DBRX shapes: faster up
-    // to 256 tokens, even at 1024, slower at 4096)
-    const int64_t chain_waves =
-        d.tokens * ((d.experts + 4 * chain_requests(d) - 1) / (4 * chain_requests(d)));
-    if (chain_waves <= kRouteChainMaxWaves && chain_fits(d) && ((uintptr_t)x & 15) == 0 &&
-        (d.experts <= 16 || logits))
-        return launch_chain(d, x, wr, bias, ids, w, logits, s);
-    if (d.experts <= 16) return launch_lane_router(d, x, wr, bias, ids, w, s);
-    // many experts, up to kRouteLogitsMaxTokens tokens: the register-tiled
-    // kernel has too few workgroups to cover its serial h loop (or, up to
-    // 4096 tokens, issues more instructions per chain than the lane kernel
-    // does in parallel), so the lane-per-token kernel takes blocks of 16
-    // experts per workgroup (logits through the caller's buffer, then the
-    // selection kernel)
-    if (logits && d.tokens <= kRouteLogitsMaxTokens)
-        return launch_lane_z<2, 2, 4>(d, x, wr, bias, ids, w, logits, s);
-    // 129..160 experts below 65536 tokens: 32 expert groups of 5, with the
-    // most tokens per thread that keeps ~2 waves per SIMD (T / 4096, at most
-    // 4).  Against 16 groups of 10 it reads fewer operands per fma at equal
-    // occupancy, or doubles the occupancy of small batches (E = 160,
-    // measured: T = 4096 279 vs 333 us, 16384 502 vs 577 us, 32768 938 vs
-    // 1094 us).  From 65536 tokens 16 groups of 10 x 4 tokens is faster.
-    if (d.experts > 128 && d.experts <= 160 && d.tokens < 65536) {
-        if (d.tokens >= 16384) return launch_tt<5, 4, 32>(d, x, wr, bias, ids, w, s);
-        if (d.tokens >= 8192) return launch_tt<5, 2, 32>(d, x, wr, bias, ids, w, s);
-        return launch_tt<5, 1, 32>(d, x, wr, bias, ids, w, s);
+    // the LDS-DMA of the matrix-core and chain kernels copies 16-byte pieces
+    // at 32-bit offsets from a workgroup's first row
+    const bool aligned =
+        (((uintptr_t)x | (uintptr_t)wr) & 15) == 0 && d.hidden <= kRouteDmaMaxHidden;
+    if (aligned) {
+        // up to 512 tokens of at most 16 experts: a chain per lane, whose
+        // dependent fma is shorter than a quarter of the matrix core's (us,
+        // chain against matrix core: Mixtral 64 tokens 16.2 / 21.6, 512
+        // tokens 19.9 / 22.1; DBRX 512 tokens 30.0 / 32.4)
+        if (d.tokens <= kRouteChainMaxTokens && chain_fits(d))
+            return launch_chain(d, x, wr, bias, ids, w, s);
+        return launch_mfma_router(d, x, wr, bias, ids, w, logits, s);
     }
+    // any alignment: the lane-per-token kernel, or the register-tiled one
+    // for more than 16 experts
+    if (d.experts <= 16) return launch_lane_router(d, x, wr, bias, ids, w, s);
     const int te = (d.experts + 15) / 16;
     if (te <= 2) return launch_te<2>(d, x, wr, bias, ids, w, s);
     if (te <= 4) return launch_te<4>(d, x, wr, bias, ids, w, s);

@@ -1,0 +1,76 @@
+"""The matrix-core router against the oracle, bit for bit: every workgroup
+shape its rule picks, ragged token and expert blocks, one to many stages,
+masked experts, and the kernels that take over for operands that are not
+16-byte aligned."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2410_12247_amd import moe, synth
+from tests.gpu_util import bf16, dev, f32
+
+pytestmark = pytest.mark.gpu
+
+
+def draw(T, E, H, use_bias, seed):
+    rng = np.random.default_rng(seed)
+    xb = synth.bf16_bits(rng.standard_normal((T, H), dtype=np.float32))
+    wr = rng.standard_normal((E, H), dtype=np.float32) * np.float32(0.05)
+    bias = rng.standard_normal(E, dtype=np.float32) * np.float32(0.1) if use_bias else None
+    return xb, wr, bias
+
+
+def check(x, w_router, bias, want_ids, want_w, T, E, H, k, renorm):
+    d = moe.dims(T, H, 64, E, k, renormalize=renorm)
+    ids = torch.full((T, k), -1, dtype=torch.int32, device=dev())
+    w = torch.full((T, k), -1.0, dtype=torch.float32, device=dev())
+    moe.route(d, x, w_router, bias, ids, w)
+    torch.cuda.synchronize()
+    assert np.array_equal(ids.cpu().numpy(), want_ids)
+    # the fp64 softmax rounds once to fp32: at most one unit in the last place
+    np.testing.assert_array_max_ulp(w.cpu().numpy(), want_w, maxulp=1)
+
+
+@pytest.mark.parametrize("T,E,H,k,renorm,use_bias", [
+    (513, 8, 64, 2, True, False),       # E <= 16: one wave per workgroup, one stage
+    (4095, 16, 320, 8, False, True),    # its last full block, stages not a multiple of the ring
+    (4097, 13, 128, 3, True, True),     # four waves
+    (1, 17, 64, 8, True, False),        # one token, a block of one expert
+    (33, 33, 192, 2, False, True),      # 16 tokens x 4 waves of experts
+    (4097, 64, 64, 8, True, False),     # 32 tokens
+    (8193, 160, 128, 6, False, True),   # 64 tokens, a ragged last workgroup
+    (33000, 160, 64, 6, True, False),   # 128 tokens
+    (9000, 208, 64, 5, True, True),     # 13 blocks of experts in two waves of 8
+    (300, 256, 448, 8, False, False),   # the most experts
+])
+def test_shapes(T, E, H, k, renorm, use_bias):
+    xb, wr, bias = draw(T, E, H, use_bias, 31 * T + E)
+    _, ids, w = oracle.route(xb, wr, bias, k, renorm)
+    check(bf16(xb), f32(wr), f32(bias) if use_bias else None, ids, w, T, E, H, k, renorm)
+
+
+@pytest.mark.parametrize("T,E", [(5, 8), (700, 8), (600, 160)])
+def test_masked_experts(T, E):
+    """Experts masked by a bias of -inf or the lowest float are never chosen
+    and weigh nothing in the full softmax."""
+    xb, wr, bias = draw(T, E, 128, True, T + E)
+    bias[1::4] = -np.inf
+    bias[2::4] = np.finfo(np.float32).min
+    _, ids, w = oracle.route(xb, wr, bias, 3, False)
+    check(bf16(xb), f32(wr), f32(bias), ids, w, T, E, 128, 3, False)
+
+
+@pytest.mark.parametrize("E", [40, 160])
+def test_unaligned_rows(E):
+    """x eight bytes off a 16-byte boundary."""
+    T, H, k = 600, 192, 4
+    xb, wr, bias = draw(T, E, H, True, E)
+    _, ids, w = oracle.route(xb, wr, bias, k, True)
+    buf = torch.empty(T * H + 4, dtype=torch.bfloat16, device=dev())
+    x = buf[4:].view(T, H)
+    x.copy_(bf16(xb))
+    assert x.data_ptr() % 16 == 8
+    check(x, f32(wr), f32(bias), ids, w, T, E, H, k, True)
