@@ -7,9 +7,9 @@
 // Both operands are contiguous along the reduced dimension.  The MFMA is
 // fed the WEIGHT rows as its first (row) operand and the TOKEN rows as its
 // second (column) operand, so each lane ends up holding four consecutive
-// output features of one token row: a 16-byte fp32 store (down) or an
-// 8-byte bf16 store (gate/up), and for gate/up the matching gate and up
-// values sit in the same lane, so SiLU*mul needs no data movement.
+// output features of one token row, and for gate/up the matching gate and up
+// values sit in the same lane, so SiLU*mul needs no data movement.  The
+// outputs leave through LDS as whole row segments (tile_epilogue).
 //
 // Workgroup tile (the one both schedulers use): 256 weight rows x 320 token
 // rows, eight waves in two groups that alternate between MFMAs and memory
@@ -17,9 +17,7 @@
 // K advances 32 per stage through four LDS stages filled by LDS-DMA loads,
 // so the loads of the next three stages are in flight while a stage is
 // multiplied.  16-byte chunks of each LDS row are XOR-swizzled so MFMA
-// operand reads hit distinct banks.  A four-wave tile (2 x 2 waves, one per
-// SIMD, accumulators in AGPRs) is kept as the alternative selected with
-// MOE_GEMM_PINGPONG=0; it is slower on the expert shapes measured.
+// operand reads hit distinct banks.
 //
 // Two schedulers share that tile code and its arithmetic (so both give the
 // same bits for the same rows):
@@ -35,15 +33,11 @@
 #include <cmath>
 #include <type_traits>
 
-#include "common.h"
+#include "lds_dma.h"
 
 namespace moe {
 namespace {
 
-typedef __attribute__((address_space(3))) void lds_void_t;
-typedef __attribute__((address_space(1))) void gbl_void_t;
-
-constexpr int NTHREADS = 256;
 constexpr int NXCD = 8;
 constexpr int GROUP_N = 8;  // n-tiles per super-column of the tile order
 
@@ -61,27 +55,6 @@ __device__ __forceinline__ void wait_vmcnt() {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-template <int MODE, int BN, int BM, int BK, int NS>
-struct Cfg {
-    static constexpr int WN = 2, WM = 2;
-    static constexpr int WTN = BN / WN;  // weight rows per wave
-    static constexpr int WTM = BM / WM;  // token rows per wave
-    static constexpr int TN = WTN / 16;  // 16-row MFMA tiles along weights
-    static constexpr int TM = WTM / 16;  // 16-row MFMA tiles along tokens
-    static constexpr int CPR = BK / 8;   // 16-byte chunks per LDS row
-    static constexpr int RPI = 64 / CPR; // rows one wave-wide LDS-DMA fills
-    static constexpr int W_INSTR = BN / 4 / RPI;  // DMA instructions per wave per stage
-    static constexpr int X_INSTR = BM / 4 / RPI;
-    static constexpr int LPS = W_INSTR + X_INSTR;
-    static constexpr int STAGE_W = BN * BK;  // bf16 elements per stage
-    static constexpr int STAGE_X = BM * BK;
-    static constexpr int STAGE = STAGE_W + STAGE_X;
-    // output columns one tile covers: act columns (gate/up) or features (down)
-    static constexpr int BNOUT = MODE == 0 ? BN / 2 : BN;
-    static_assert((NS - 2) * LPS <= 63, "vmcnt range");
-    static_assert(BN % (4 * RPI) == 0 && BM % (4 * RPI) == 0, "DMA tiling");
-};
-
 struct TileArgs {
     const bf16_t *w0;  // first weight row of the tile (gate rows, or down rows)
     const bf16_t *w1;  // first up row (gate/up only)
@@ -96,10 +69,8 @@ struct TileArgs {
     int k0, nks;       // K stages [k0, k0 + nks) of BK elements this call covers
     void *out;         // output element (first token row, first column)
     int64_t ldo;       // output row stride in elements
-    // K split (npieces > 1): this call is piece `piece` of the tile and
-    // stores its fp32 accumulators in part[piece] instead of the output
+    // K split: the piece's fp32 accumulators go here instead (NULL: whole K)
     float *part;
-    int piece, npieces;
 };
 
 __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
@@ -121,211 +92,6 @@ __device__ __forceinline__ float silu_mul(float g, float u) {
     return g * __builtin_amdgcn_rcpf(1.0f + e) * u;
 }
 
-// One output tile.  Global -> LDS copies are wave-wide LDS-DMA loads
-// (global_load_lds_dwordx4: lane l's 16 bytes land at base + 16*l, no
-// registers involved); each wave fills its quarter of the weight and token
-// rows of a stage.  NS stages are in flight: stage kt+NS-1 is requested
-// while stage kt is multiplied, and a wave only waits (vmcnt) for the stage
-// it needs next.
-template <int MODE, int BN, int BM, int BK, int NS>
-__device__ __forceinline__ void run_tile(const TileArgs &a, bf16_t *smem) {
-    using C = Cfg<MODE, BN, BM, BK, NS>;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    // wave index as a scalar: everything derived from it (LDS-DMA targets,
-    // which weight half a wave copies) stays in SGPRs
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wn = wave % C::WN;
-    const int wm = wave / C::WN;
-    const int K = a.K;
-    const int nk = K / BK;
-
-    floatx4 acc[C::TN][C::TM];
-#pragma unroll
-    for (int t = 0; t < C::TN; ++t)
-#pragma unroll
-        for (int m = 0; m < C::TM; ++m) acc[t][m] = floatx4{0.f, 0.f, 0.f, 0.f};
-
-    // ---- LDS-DMA assignment: this wave fills weight rows
-    //      [wave*BN/4, (wave+1)*BN/4) and token rows [wave*BM/4, ...).
-    const int drow = lane / C::CPR;                               // row within one DMA
-    const int dchunk = ((lane % C::CPR) ^ swz<BK>(drow)) * 8;     // logical k offset
-    const bf16_t *wsrc;
-    int wrow0;
-    if (MODE == 0) {
-        // waves 0..1 copy gate rows, waves 2..3 copy up rows
-        const bool up = wave >= 2;
-        wsrc = up ? a.w1 : a.w0;
-        wrow0 = (wave & 1) * (BN / 4);
-    } else {
-        wsrc = a.w0;
-        wrow0 = wave * (BN / 4);
-    }
-    // per-lane byte offsets from the (scalar) tile base; rows past the valid
-    // range read a valid row, whose results are never stored
-    uint32_t woff[C::W_INSTR];
-#pragma unroll
-    for (int i = 0; i < C::W_INSTR; ++i) {
-        const int r = min(wrow0 + i * C::RPI + drow, a.n_valid - 1);
-        woff[i] = (uint32_t)(r * K + dchunk) * 2u;
-    }
-    uint32_t xoff[C::X_INSTR];
-#pragma unroll
-    for (int i = 0; i < C::X_INSTR; ++i) {
-        const int r = min(wave * (BM / 4) + i * C::RPI + drow, a.m_valid - 1);
-        const int64_t src = a.rows ? (int64_t)(a.rows[r] / a.slot_div) : r;
-        xoff[i] = (uint32_t)((src * K + dchunk) * 2);
-    }
-    const int w_lds = wave * (BN / 4) * BK;  // element offset of this wave's rows
-    const int x_lds = C::STAGE_W + wave * (BM / 4) * BK;
-
-    // scalar base + per-lane 32-bit offset: the SADDR form of the load
-    auto issue = [&](int stage, int k0) {
-        bf16_t *sb = smem + stage * C::STAGE;
-        const char *wk = reinterpret_cast<const char *>(wsrc + k0);
-        const char *xk = reinterpret_cast<const char *>(a.x + k0);
-#pragma unroll
-        for (int i = 0; i < C::W_INSTR; ++i)
-            __builtin_amdgcn_global_load_lds((gbl_void_t *)(wk + woff[i]),
-                                             (lds_void_t *)(sb + w_lds + i * C::RPI * BK), 16,
-                                             0, 0);
-#pragma unroll
-        for (int i = 0; i < C::X_INSTR; ++i)
-            __builtin_amdgcn_global_load_lds((gbl_void_t *)(xk + xoff[i]),
-                                             (lds_void_t *)(sb + x_lds + i * C::RPI * BK), 16,
-                                             0, 0);
-    };
-
-    // ---- fragment rows (LDS row of lane 0 of each 16-row MFMA tile)
-    int arow[C::TN];
-#pragma unroll
-    for (int t = 0; t < C::TN; ++t) {
-        if (MODE == 0) {
-            arow[t] = t < C::TN / 2 ? wn * (C::WTN / 2) + t * 16
-                                    : BN / 2 + wn * (C::WTN / 2) + (t - C::TN / 2) * 16;
-        } else {
-            arow[t] = wn * C::WTN + t * 16;
-        }
-    }
-    const int lrow = lane & 15;
-    const int lk = lane >> 4;  // which 8-wide k group of the 32-wide MFMA step
-    const int lsw = swz<BK>(lrow);
-
-    // Operand fragments are double-buffered in registers: while the MFMAs
-    // of stage kt run, the fragments of stage kt+1 are read from LDS.
-    struct Frags {
-        bf16x8 a[C::TN];
-        bf16x8 b[C::TM];
-    };
-    static_assert(BK == 32, "one 32-wide MFMA step per stage");
-    static_assert(NS == 4, "the K loop below is unrolled for four stages");
-    Frags f0, f1;
-
-    auto load_frags = [&](int stage, Frags &f) {
-        const bf16_t *sw = smem + stage * C::STAGE;
-        const bf16_t *sx = sw + C::STAGE_W;
-        const int chunk = (lk ^ lsw) * 8;
-#pragma unroll
-        for (int t = 0; t < C::TN; ++t)
-            f.a[t] = *reinterpret_cast<const bf16x8 *>(sw + (arow[t] + lrow) * BK + chunk);
-#pragma unroll
-        for (int m = 0; m < C::TM; ++m)
-            f.b[m] = *reinterpret_cast<const bf16x8 *>(
-                sx + (wm * C::WTM + m * 16 + lrow) * BK + chunk);
-    };
-    auto mfmas = [&](const Frags &f) {
-#pragma unroll
-        for (int m = 0; m < C::TM; ++m)
-#pragma unroll
-            for (int t = 0; t < C::TN; ++t)
-                acc[t][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.a[t], f.b[m], acc[t][m],
-                                                                    0, 0, 0);
-    };
-    // one LDS read issued between every (TN*TM)/(TN+TM) MFMAs
-    auto interleave = [&]() {
-        constexpr int NREAD = C::TN + C::TM;
-        constexpr int PER = (C::TN * C::TM) / NREAD;
-#pragma unroll
-        for (int i = 0; i < NREAD; ++i) {
-            if (i < C::LPS) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // VMEM read
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                  // DS read
-            __builtin_amdgcn_sched_group_barrier(0x008, PER, 0);                // MFMA
-        }
-    };
-    // stage kt lives in LDS buffer u = kt % NS and in register set cur
-    auto step = [&](int kt, int u, Frags &cur, Frags &nxt) {
-        const bool ahead = kt + NS - 1 < nk;
-        // Stage kt+NS-1 is requested unconditionally (past the end it re-reads
-        // the last stage into a buffer that is never read again), so the
-        // loads, LDS reads and MFMAs form one block the scheduler interleaves.
-        issue((u + NS - 1) % NS, (ahead ? kt + NS - 1 : nk - 1) * BK);
-        // the prefetch of stage kt+1 is unconditional: past the last stage it
-        // reads a stale (in-bounds) LDS buffer whose values are never used,
-        // which keeps a single MFMA block (accumulators stay in AGPRs)
-        load_frags((u + 1) % NS, nxt);
-        mfmas(cur);
-        interleave();
-        if (kt + 2 < nk) {
-            // stage kt+2 must be in LDS (every wave's share) before the next
-            // step reads it
-            if (ahead) wait_vmcnt<(NS - 3) * C::LPS>(); else wait_vmcnt<0>();
-            __builtin_amdgcn_s_barrier();
-        }
-    };
-
-    // prologue: stages 0..NS-2 requested; stage 0 in registers, stage 1 in LDS
-#pragma unroll
-    for (int s = 0; s < NS - 1; ++s)
-        if (s < nk) issue(s, s * BK);
-    if (nk >= NS - 1) wait_vmcnt<(NS - 2) * C::LPS>(); else wait_vmcnt<0>();
-    __builtin_amdgcn_s_barrier();
-    load_frags(0, f0);
-    if (nk >= NS - 1) wait_vmcnt<(NS - 3) * C::LPS>(); else wait_vmcnt<0>();
-    __builtin_amdgcn_s_barrier();
-
-    for (int kt0 = 0; kt0 < nk; kt0 += NS) {
-        step(kt0, 0, f0, f1);
-        if (kt0 + 1 < nk) step(kt0 + 1, 1, f1, f0);
-        if (kt0 + 2 < nk) step(kt0 + 2, 2, f0, f1);
-        if (kt0 + 3 < nk) step(kt0 + 3, 3, f1, f0);
-    }
-    __builtin_amdgcn_s_barrier();  // LDS free for the next tile of this workgroup
-
-    // ---- epilogue: lane holds output columns col..col+3 of token row `row`
-    const int lcol4 = (lane >> 4) * 4;
-    if (MODE == 0) {
-        bf16_t *out = reinterpret_cast<bf16_t *>(a.out);
-#pragma unroll
-        for (int t = 0; t < C::TN / 2; ++t) {
-            const int col = wn * (C::WTN / 2) + t * 16 + lcol4;
-#pragma unroll
-            for (int m = 0; m < C::TM; ++m) {
-                const int row = wm * C::WTM + m * 16 + lrow;
-                if (row < a.m_valid && col < a.n_valid) {
-                    const floatx4 g = acc[t][m];
-                    const floatx4 u = acc[t + C::TN / 2][m];
-                    uint2 v;
-                    v.x = pack_bf16x2(silu_mul(g[0], u[0]), silu_mul(g[1], u[1]));
-                    v.y = pack_bf16x2(silu_mul(g[2], u[2]), silu_mul(g[3], u[3]));
-                    *reinterpret_cast<uint2 *>(out + row * a.ldo + col) = v;
-                }
-            }
-        }
-    } else {
-        float *out = reinterpret_cast<float *>(a.out);
-#pragma unroll
-        for (int t = 0; t < C::TN; ++t) {
-            const int col = wn * C::WTN + t * 16 + lcol4;
-#pragma unroll
-            for (int m = 0; m < C::TM; ++m) {
-                const int row = wm * C::WTM + m * 16 + lrow;
-                if (row < a.m_valid && col < a.n_valid)
-                    *reinterpret_cast<floatx4 *>(out + row * a.ldo + col) = acc[t][m];
-            }
-        }
-    }
-}
-
 // ---------------------------------------------------------------------------
 // Eight-wave ping-pong variant.  256 (weights) x BM (tokens) output tile,
 // eight waves in two groups of four, one wave of each group on every SIMD.
@@ -341,7 +107,6 @@ __device__ __forceinline__ void run_tile(const TileArgs &a, bf16_t *smem) {
 // 128 x 80, 40 MFMAs per 13 fragment reads, 160 accumulator registers, four
 // 36 KiB stages) is the largest that fits 256 registers and 160 KiB of LDS.
 // ---------------------------------------------------------------------------
-constexpr int PP_THREADS = 512;
 // K per LDS stage of the ping-pong tile of bm token rows: 64 for the
 // 128-row tile (decode-sized launches, bound by the weight stream, read 128
 // contiguous bytes of each weight row per stage instead of 64: about 10%
@@ -352,7 +117,7 @@ constexpr int kBufferFlags = 0x00020000;
 
 template <int MODE, int BM_>
 struct PPCfg {
-    static constexpr int BN = 256, BM = BM_;
+    static constexpr int BN = 256, BM = BM_, WAVES = 8;
     static constexpr int BK = pp_stage_k(BM_);
     static constexpr int NS = BK == 64 ? 3 : 4;  // ring within 144 KB of LDS
     static constexpr int KH = BK / 32;  // MFMA K-steps per stage
@@ -371,9 +136,20 @@ struct PPCfg {
     static constexpr int LPS_A = W_INSTR + X_INSTR_A;  // DMA instructions per wave per stage
     static constexpr int LPS_B = W_INSTR + X_INSTR_B;
     static constexpr int STAGE_W = BN * BK, STAGE_X = BM * BK, STAGE = STAGE_W + STAGE_X;
-    static constexpr int LDS_ELEMS = NS * STAGE;
-    static_assert(LDS_ELEMS * 2 <= 144 * 1024, "ring within 144 KB of LDS");
-    static_assert(NS >= 3 && (NS - 2) * (LPS_A > LPS_B ? LPS_A : LPS_B) <= 63, "vmcnt range");
+    // the epilogue's scratch (one 16 x 64 block of outputs per wave, rows
+    // padded by 16 bytes) starts at the ring's last buffer: the next tile's
+    // first stages land in the others meanwhile
+    static constexpr int SCRATCH_ROW = (MODE == 0 ? 64 * 2 : 64 * 4) + 16;  // bytes
+    static constexpr int SCRATCH_WAVE = 16 * SCRATCH_ROW;
+    static constexpr int SCRATCH = (NS - 1) * STAGE * 2;  // byte offset
+    static constexpr int LDS_BYTES = NS * STAGE * 2 > SCRATCH + 8 * SCRATCH_WAVE
+                                         ? NS * STAGE * 2
+                                         : SCRATCH + 8 * SCRATCH_WAVE;
+    static constexpr int LDS_ELEMS = LDS_BYTES / 2;
+    static_assert(LDS_BYTES <= 144 * 1024, "ring within 144 KB of LDS");
+    // output stores of a whole tile per wave (fixed, whatever rows are valid)
+    static constexpr int STORES = MODE == 0 ? 2 * TM : 8 * TM;
+    static_assert(NS >= 3 && (NS - 2) * LPS_A + STORES <= 63, "vmcnt range");
     static constexpr int BNOUT = MODE == 0 ? BN / 2 : BN;
     static constexpr int PART_ELEMS = BN * BM;  // fp32 accumulators of one tile
     static constexpr int PART_BYTES = PART_ELEMS * 4;
@@ -407,208 +183,14 @@ __device__ __forceinline__ void store_down(const floatx4 &v, int t, int m, int w
     if (row < m_valid && col < n_valid) *reinterpret_cast<floatx4 *>(out + row * ldo + col) = v;
 }
 
-template <int MODE, class C>
-__device__ __forceinline__ void pp_epilogue(const floatx4 (&acc)[C::TN][C::TM], int wn, int wm,
-                                            int lane, void *outp, int64_t ldo, int m_valid,
-                                            int n_valid) {
-    if (MODE == 0) {
-#pragma unroll
-        for (int p = 0; p < C::TN / 2; ++p)
-#pragma unroll
-            for (int m = 0; m < C::TM; ++m)
-                store_gateup<C>(acc[p][m], acc[p + C::TN / 2][m], p, m, wn, wm, lane,
-                                reinterpret_cast<bf16_t *>(outp), ldo, m_valid, n_valid);
-    } else {
-#pragma unroll
-        for (int t = 0; t < C::TN; ++t)
-#pragma unroll
-            for (int m = 0; m < C::TM; ++m)
-                store_down<C>(acc[t][m], t, m, wn, wm, lane, reinterpret_cast<float *>(outp), ldo,
-                              m_valid, n_valid);
-    }
-}
-
-template <int MODE, int BM_>
-__device__ __forceinline__ void run_tile_pp(const TileArgs &a, bf16_t *smem) {
-    using C = PPCfg<MODE, BM_>;
-    constexpr int BK = C::BK, NS = C::NS;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int grp = wave >> 2;  // 0 = A, 1 = B
-    const int wn = wave & 1;    // weight half
-    const int wm = wave >> 1;   // 64-row token block
-    const int K = a.K;
-    const int nk = a.nks;
-    // a wave whose token rows or weight rows all lie past the valid edge of
-    // a partial tile skips its MFMAs (its outputs are never stored); it still
-    // takes its share of the loads and barriers
-    const bool active = wm * C::WTM < a.m_valid &&
-                        (MODE == 0 ? wn * (C::WTN / 2) : wn * C::WTN) < a.n_valid;
-
-    floatx4 acc[C::TN][C::TM];
-#pragma unroll
-    for (int t = 0; t < C::TN; ++t)
-#pragma unroll
-        for (int m = 0; m < C::TM; ++m) acc[t][m] = floatx4{0.f, 0.f, 0.f, 0.f};
-
-    // ---- LDS-DMA share of this wave: BN/8 weight rows and a slice of the
-    // token rows (BM/16 instructions of 16 rows split over the waves,
-    // group A's waves taking the larger slices when they do not divide evenly)
-    const int drow = lane / C::CPR;
-    const int dchunk = ((lane % C::CPR) ^ swz<BK>(drow)) * 8;
-    const bf16_t *wsrc;
-    int wrow0;
-    if (MODE == 0) {  // waves 0..3 copy gate rows, 4..7 up rows
-        wsrc = wave >= 4 ? a.w1 : a.w0;
-        wrow0 = (wave & 3) * (C::BN / 8);
-    } else {
-        wsrc = a.w0;
-        wrow0 = wave * (C::BN / 8);
-    }
-    uint32_t woff[C::W_INSTR], xoff[C::X_INSTR_A];
-#pragma unroll
-    for (int i = 0; i < C::W_INSTR; ++i) {
-        const int r = min(wrow0 + i * C::RPI + drow, a.n_valid - 1);
-        woff[i] = (uint32_t)(r * K + dchunk) * 2u;
-    }
-    // first token row of this wave's LDS-DMA share
-    const int x_row0 = grp == 0 ? wave * C::X_INSTR_A * C::RPI
-                                : 4 * C::X_INSTR_A * C::RPI + (wave - 4) * C::X_INSTR_B * C::RPI;
-#pragma unroll
-    for (int i = 0; i < C::X_INSTR_A; ++i) {
-        const int r = min(x_row0 + i * C::RPI + drow, a.m_valid - 1);
-        const int64_t src = a.rows ? (int64_t)(a.rows[r] / a.slot_div) : r;
-        xoff[i] = (uint32_t)((src * K + dchunk) * 2);
-    }
-    const int w_lds = wave * (C::BN / 8) * BK;
-    const int x_lds = C::STAGE_W + x_row0 * BK;
-    // this wave's share of stage kstage (clamped); nx: its token-row
-    // instruction count (the group's)
-    // buffer resources over the weight rows and the token rows: a 32-bit
-    // per-lane row offset plus the stage's k offset as the scalar offset
-    const __amdgpu_buffer_rsrc_t wres =
-        __builtin_amdgcn_make_buffer_rsrc((void *)wsrc, 0, -1, kBufferFlags);
-    const __amdgpu_buffer_rsrc_t xres =
-        __builtin_amdgcn_make_buffer_rsrc((void *)a.x, 0, -1, kBufferFlags);
-    auto issue = [&](int kstage, auto nx) {
-        const int ks = min(kstage, nk - 1);
-        bf16_t *sb = smem + (kstage % NS) * C::STAGE;
-        const int kb = (a.k0 + ks) * BK * 2;
-#pragma unroll
-        for (int i = 0; i < C::W_INSTR; ++i)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                wres, (lds_void_t *)(sb + w_lds + i * C::RPI * BK), 16, woff[i], kb, 0, 0);
-#pragma unroll
-        for (int i = 0; i < decltype(nx)::value; ++i)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                xres, (lds_void_t *)(sb + x_lds + i * C::RPI * BK), 16, xoff[i], kb, 0, 0);
-    };
-
-    // ---- fragments of this wave
-    int arow[C::TN];
-#pragma unroll
-    for (int t = 0; t < C::TN; ++t) {
-        if (MODE == 0)
-            arow[t] = t < C::TN / 2 ? wn * (C::WTN / 2) + t * 16
-                                    : C::BN / 2 + wn * (C::WTN / 2) + (t - C::TN / 2) * 16;
-        else
-            arow[t] = wn * C::WTN + t * 16;
-    }
-    const int lrow = lane & 15;
-    // the chunk holding K 32 h + 8 (lane / 16) .. + 7 of a row, K-step h
-    int chunk[C::KH];
-#pragma unroll
-    for (int h = 0; h < C::KH; ++h) chunk[h] = ((h * 4 + (lane >> 4)) ^ swz<BK>(lrow)) * 8;
-    bf16x8 fa[C::KH][C::TN], fb[C::KH][C::TM];
-    auto load_frags = [&](int kstage) {  // stale but in-bounds past the end
-        const bf16_t *sw = smem + (kstage % NS) * C::STAGE;
-        const bf16_t *sx = sw + C::STAGE_W;
-#pragma unroll
-        for (int h = 0; h < C::KH; ++h) {
-#pragma unroll
-            for (int t = 0; t < C::TN; ++t)
-                fa[h][t] =
-                    *reinterpret_cast<const bf16x8 *>(sw + (arow[t] + lrow) * BK + chunk[h]);
-#pragma unroll
-            for (int m = 0; m < C::TM; ++m)
-                fb[h][m] = *reinterpret_cast<const bf16x8 *>(
-                    sx + (wm * C::WTM + m * 16 + lrow) * BK + chunk[h]);
-        }
-    };
-    auto mfmas = [&]() {  // K-steps in ascending order
-#pragma unroll
-        for (int h = 0; h < C::KH; ++h)
-#pragma unroll
-            for (int m = 0; m < C::TM; ++m)
-#pragma unroll
-                for (int t = 0; t < C::TN; ++t)
-                    acc[t][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[h][t], fb[h][m],
-                                                                        acc[t][m], 0, 0, 0);
-    };
-
-    // prologue: stages 0 .. NS-2 requested by every wave, all landed
-    using nxa = std::integral_constant<int, C::X_INSTR_A>;
-    using nxb = std::integral_constant<int, C::X_INSTR_B>;
-#pragma unroll
-    for (int s = 0; s < NS - 1; ++s) {
-        if (grp == 0) issue(s, nxa{}); else issue(s, nxb{});
-    }
-    wait_vmcnt<0>();
-    __builtin_amdgcn_s_barrier();
-
-    // the two groups' loops, with or without the MFMAs; each is straight
-    // code (no branch around the MFMA block inside the loop)
-    auto loop_a = [&](auto with_mfma) {
-        load_frags(0);
-        for (int k = 0; k < nk; ++k) {
-            // compute phase: stage k
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            __builtin_amdgcn_s_setprio(1);
-            if constexpr (decltype(with_mfma)::value) mfmas();
-            __builtin_amdgcn_s_setprio(0);
-            // stage k+1 landed before the barrier; this wave's requests for
-            // stages k+2 .. k+NS-2 may stay in flight
-            wait_vmcnt<(NS - 3) * C::LPS_A>();
-            __builtin_amdgcn_s_barrier();
-            // memory phase: fragments of stage k+1, this wave's share of stage k+NS-1
-            load_frags(k + 1);
-            issue(k + NS - 1, nxa{});
-            __builtin_amdgcn_s_barrier();
-        }
-    };
-    auto loop_b = [&](auto with_mfma) {
-        for (int k = 0; k < nk; ++k) {
-            // memory phase: fragments of stage k, this wave's share of stage k+NS-1
-            load_frags(k);
-            issue(k + NS - 1, nxb{});
-            // stage k+1 landed; this wave's requests for stages k+2 ..
-            // k+NS-1 (the last just issued) may stay in flight
-            wait_vmcnt<(NS - 2) * C::LPS_B>();
-            __builtin_amdgcn_s_barrier();
-            // compute phase: stage k
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            __builtin_amdgcn_s_setprio(1);
-            if constexpr (decltype(with_mfma)::value) mfmas();
-            __builtin_amdgcn_s_setprio(0);
-            __builtin_amdgcn_s_barrier();
-        }
-    };
-    using on = std::integral_constant<bool, true>;
-    using off = std::integral_constant<bool, false>;
-    if (grp == 0) {
-        if (active) loop_a(on{}); else loop_a(off{});
-    } else {
-        if (active) loop_b(on{}); else loop_b(off{});
-    }
-    wait_vmcnt<0>();  // clamped tail requests drained before LDS is reused
-    __builtin_amdgcn_s_barrier();
-
-    // ---- K split: the piece stores its accumulators (each wave its own
-    // block, one 1 KiB store per fragment, through a buffer resource so the
+    // K split: the piece stores its accumulators (each wave its own block,
+    // one 1 KiB store per fragment, through a buffer resource so the
     // fragment offsets are scalars); split_fixup_kernel adds the pieces and
     // runs the epilogue
-    if (a.npieces > 1) {
+    template <class C>
+__device__ __forceinline__ void tile_store_piece(const floatx4 (&acc)[C::TN][C::TM], int wave,
+                                                 const TileArgs &a) {
+    const int wm = wave >> 1, lane = threadIdx.x & 63;
         const __amdgpu_buffer_rsrc_t pres =
             __builtin_amdgcn_make_buffer_rsrc(a.part, 0, -1, kBufferFlags);
         const int loff = lane * 16;
@@ -622,13 +204,321 @@ __device__ __forceinline__ void run_tile_pp(const TileArgs &a, bf16_t *smem) {
             for (int t = 0; t < C::TN; ++t)
                 __builtin_amdgcn_raw_buffer_store_b128(
                     __builtin_bit_cast(u32x4, acc[t][m]), pres, loff,
-                    a.piece * C::PART_BYTES + wave * C::WAVE_BYTES + (t * C::TM + m) * 1024, 0);
+                    wave * C::WAVE_BYTES + (t * C::TM + m) * 1024, 0);
         }
-        return;
     }
 
-    pp_epilogue<MODE, C>(acc, wn, wm, lane, a.out, a.ldo, a.m_valid, a.n_valid);
-}
+    // Outputs of a whole tile.  A fragment leaves the MFMA with four columns of
+// 16 rows per lane; stored as it is, a request would scatter 16-byte (down)
+// or 8-byte (gate/up) pieces over 16 rows, each its own trip to the L2.  So
+// 16 x 64 blocks go through the wave's LDS scratch and leave as whole row
+// segments (256 or 128 bytes).  Every store is issued, whatever rows are
+// valid: lanes without a valid row get an offset past the resource's range,
+// which drops them.  With the next tile's first stages requested before
+// (PPTile), down GEMM us, scattered stores after the K loop -> this: DBRX
+// 8192 tokens 632 -> 576, Mixtral 16384 tokens 864 -> 831; dense FFN of 3001
+// rows x 5120 x 3072 237 -> 226; non-temporal stores: within 1%.
+template <int MODE, class C>
+__device__ __forceinline__ void tile_epilogue(const floatx4 (&acc)[C::TN][C::TM], bf16_t *smem,
+                                              int wave, const TileArgs &a) {
+    const int wn = wave & 1, wm = wave >> 1;
+        // (an opaque lane index: addresses computed from it are not hoisted
+        // over the K loop, which has no register to spare for them)
+        int lane = threadIdx.x & 63;
+        asm volatile("" : "+v"(lane));
+        char *sc = reinterpret_cast<char *>(smem) + C::SCRATCH + wave * C::SCRATCH_WAVE;
+        constexpr uint32_t RANGE = 0xFFFFFFF0u, DROP = 0xFFFFFFF8u;
+        const __amdgpu_buffer_rsrc_t ores =
+            __builtin_amdgcn_make_buffer_rsrc(a.out, 0, (int)RANGE, kBufferFlags);
+        const int row_w = (lane & 15) * C::SCRATCH_ROW;  // write: row lane % 16
+        if (MODE == 0) {
+            const int rr = lane >> 3, rc = lane & 7;  // read: 8 rows x 8 chunks of 16 bytes
+            const uint32_t colb = (uint32_t)(wn * 64 + rc * 8) * 2u;
+            const bool cols = wn * 64 < a.n_valid;
+#pragma unroll
+            for (int m = 0; m < C::TM; ++m) {
+#pragma unroll
+                for (int p = 0; p < 4; ++p) {
+                    const floatx4 g = acc[p][m], u = acc[p + 4][m];
+                    uint2 v;
+                    v.x = pack_bf16x2(silu_mul(g[0], u[0]), silu_mul(g[1], u[1]));
+                    v.y = pack_bf16x2(silu_mul(g[2], u[2]), silu_mul(g[3], u[3]));
+                    *reinterpret_cast<uint2 *>(sc + row_w + p * 32 + (lane >> 4) * 8) = v;
+                }
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const u32x4 v = *reinterpret_cast<const u32x4 *>(
+                        sc + (i * 8 + rr) * C::SCRATCH_ROW + rc * 16);
+                    const int row = wm * C::WTM + m * 16 + i * 8 + rr;
+                    const uint32_t off = cols && row < a.m_valid
+                                             ? (uint32_t)(row * a.ldo) * 2u + colb
+                                             : DROP;
+                    __builtin_amdgcn_raw_buffer_store_b128(v, ores, off, 0, 0);
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+        } else {
+            const int rr = lane >> 4, rc = lane & 15;  // read: 4 rows x 16 chunks
+#pragma unroll
+            for (int m = 0; m < C::TM; ++m)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const bool cols = wn * 128 + h * 64 < a.n_valid;
+                    const uint32_t colb = (uint32_t)(wn * 128 + h * 64 + rc * 4) * 4u;
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        *reinterpret_cast<floatx4 *>(sc + row_w + t * 64 + (lane >> 4) * 16) =
+                            acc[h * 4 + t][m];
+                    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const u32x4 v = *reinterpret_cast<const u32x4 *>(
+                            sc + (i * 4 + rr) * C::SCRATCH_ROW + rc * 16);
+                        const int row = wm * C::WTM + m * 16 + i * 4 + rr;
+                        const uint32_t off = cols && row < a.m_valid
+                                                 ? (uint32_t)(row * a.ldo) * 4u + colb
+                                                 : DROP;
+                        __builtin_amdgcn_raw_buffer_store_b128(v, ores, off, 0, 0);
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                }
+        }
+    }
+
+// A workgroup's walk over its tiles: bind (operand addresses of a tile),
+// prologue (its first NS - 1 stages requested), kloop, epilogue.  The next
+// tile is bound and its prologue issued before the current tile's epilogue,
+// so its first stages land while the outputs are written, and the waits of
+// its first stages leave the stores, which are younger, in flight (loads and
+// stores share one in-order vmcnt).
+template <int MODE, int BM_>
+struct PPTile {
+    using C = PPCfg<MODE, BM_>;
+    static constexpr int BK = C::BK, NS = C::NS;
+    bf16_t *smem;
+    uint32_t lds0;
+    int lane, wave, grp, wn, wm;
+    int k0, nk;       // K stages of the tile
+    bool active;
+    u32x4 wres, xres;  // buffer resources over the weight rows and the token rows
+    uint32_t woff[C::W_INSTR], xoff[C::X_INSTR_A];
+    floatx4 acc[C::TN][C::TM];
+
+    __device__ __forceinline__ explicit PPTile(bf16_t *sm) : smem(sm) {
+        lds0 = (uint32_t)(uintptr_t)(lds_void_t *)sm;
+        lane = threadIdx.x & 63;
+        wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        grp = wave >> 2;  // 0 = A, 1 = B
+        wn = wave & 1;    // weight half
+        wm = wave >> 1;   // token block
+    }
+
+    // first token row of this wave's LDS-DMA share
+    __device__ __forceinline__ int x_row0() const {
+        return grp == 0 ? wave * C::X_INSTR_A * C::RPI
+                        : 4 * C::X_INSTR_A * C::RPI + (wave - 4) * C::X_INSTR_B * C::RPI;
+    }
+
+    // LDS-DMA share of this wave: BN/8 weight rows and a slice of the token
+    // rows (group A's waves taking the larger slices when they do not divide
+    // evenly); a 32-bit per-lane row offset, the stage's k offset is scalar
+    __device__ __forceinline__ void bind(const TileArgs &a) {
+        k0 = a.k0;
+        nk = a.nks;
+        // a wave whose token rows or weight rows all lie past the valid edge
+        // of a partial tile skips its MFMAs (its outputs are never stored);
+        // it still takes its share of the loads and barriers
+        active = wm * C::WTM < a.m_valid &&
+                 (MODE == 0 ? wn * (C::WTN / 2) : wn * C::WTN) < a.n_valid;
+        int lane = threadIdx.x & 63;  // opaque, as in the epilogue
+        asm volatile("" : "+v"(lane));
+        const int drow = lane / C::CPR;
+        const int dchunk = ((lane % C::CPR) ^ swz<BK>(drow)) * 8;
+        int wrow0;
+        if (MODE == 0) {  // waves 0..3 copy gate rows, 4..7 up rows
+            wres = buf_rsrc(wave >= 4 ? a.w1 : a.w0);
+            wrow0 = (wave & 3) * (C::BN / 8);
+        } else {
+            wres = buf_rsrc(a.w0);
+            wrow0 = wave * (C::BN / 8);
+        }
+        xres = buf_rsrc(a.x);
+#pragma unroll
+        for (int i = 0; i < C::W_INSTR; ++i) {
+            const int r = min(wrow0 + i * C::RPI + drow, a.n_valid - 1);
+            woff[i] = (uint32_t)(r * a.K + dchunk) * 2u;
+        }
+#pragma unroll
+        for (int i = 0; i < C::X_INSTR_A; ++i) {
+            const int r = min(x_row0() + i * C::RPI + drow, a.m_valid - 1);
+            const int64_t src = a.rows ? (int64_t)(a.rows[r] / a.slot_div) : r;
+            xoff[i] = (uint32_t)((src * a.K + dchunk) * 2);
+        }
+    }
+
+    // this wave's share of stage ks (nx: its token-row instruction count,
+    // the group's) into the stage's buffer
+    template <class NX>
+    __device__ __forceinline__ void issue(int ks, NX) {
+        const uint32_t sb = lds0 + (uint32_t)((ks % NS) * C::STAGE * 2);
+        const uint32_t kb = (uint32_t)((k0 + ks) * BK * 2);
+#pragma unroll
+        for (int i = 0; i < C::W_INSTR; ++i)
+            buf16_to_lds(wres, woff[i], kb, sb + (wave * (C::BN / 8) + i * C::RPI) * BK * 2);
+#pragma unroll
+        for (int i = 0; i < NX::value; ++i)
+            buf16_to_lds(xres, xoff[i], kb,
+                         sb + C::STAGE_W * 2 + (x_row0() + i * C::RPI) * BK * 2);
+    }
+    using nxa = std::integral_constant<int, C::X_INSTR_A>;
+    using nxb = std::integral_constant<int, C::X_INSTR_B>;
+
+    // stages 0 .. NS-2 requested (a shorter tile repeats its last stage)
+    __device__ __forceinline__ void prologue() {
+#pragma unroll
+        for (int s = 0; s < NS - 1; ++s) {
+            // (the copy of stage nk-1 goes to a buffer nothing reads)
+            const int back = max(s - (nk - 1), 0);
+            k0 -= back;
+            if (grp == 0) issue(s, nxa{}); else issue(s, nxb{});
+            k0 += back;
+        }
+    }
+
+    // What this wave sent after the prologue's requests.
+    enum After { NOTHING, STORES, PIECE };
+
+    // The K loop; every wave leaves it with the ring free and no request in
+    // flight.
+    __device__ __forceinline__ void kloop(After after) {
+#pragma unroll
+        for (int t = 0; t < C::TN; ++t)
+#pragma unroll
+            for (int m = 0; m < C::TM; ++m) acc[t][m] = floatx4{0.f, 0.f, 0.f, 0.f};
+        // stage 0 landed (a piece's stores vary in number: everything landed)
+        if (after == PIECE)
+            wait_vmcnt<0>();
+        else if (after == STORES && grp == 0)
+            wait_vmcnt<(NS - 2) * C::LPS_A + C::STORES>();
+        else if (after == STORES)
+            wait_vmcnt<(NS - 2) * C::LPS_B + C::STORES>();
+        else if (grp == 0)
+            wait_vmcnt<(NS - 2) * C::LPS_A>();
+        else
+            wait_vmcnt<(NS - 2) * C::LPS_B>();
+        __builtin_amdgcn_s_barrier();
+        // the two groups' loops, with or without the MFMAs; each is straight
+        // code (no branch around the MFMA block inside the loop)
+        using on = std::integral_constant<bool, true>;
+        using off = std::integral_constant<bool, false>;
+        const bool stored = after == STORES;
+        if (grp == 0) {
+            if (active) loop_a(stored, on{}); else loop_a(stored, off{});
+        } else {
+            if (active) loop_b(stored, on{}); else loop_b(stored, off{});
+        }
+    }
+
+    // fragments of this wave: the chunk holding K 32 h + 8 (lane / 16) .. + 7
+    // of a row, K-step h
+    struct Frags {
+        bf16x8 a[C::KH][C::TN], b[C::KH][C::TM];
+    };
+    __device__ __forceinline__ void load_frags(Frags &f, int ks) {
+        const bf16_t *sw = smem + (ks % NS) * C::STAGE;
+        const bf16_t *sx = sw + C::STAGE_W;
+        const int lrow = lane & 15;
+#pragma unroll
+        for (int h = 0; h < C::KH; ++h) {
+            const int chunk = ((h * 4 + (lane >> 4)) ^ swz<BK>(lrow)) * 8;
+#pragma unroll
+            for (int t = 0; t < C::TN; ++t) {
+                const int arow = MODE == 0 ? (t < C::TN / 2
+                                                  ? wn * (C::WTN / 2) + t * 16
+                                                  : C::BN / 2 + wn * (C::WTN / 2) +
+                                                        (t - C::TN / 2) * 16)
+                                           : wn * C::WTN + t * 16;
+                f.a[h][t] = *reinterpret_cast<const bf16x8 *>(sw + (arow + lrow) * BK + chunk);
+            }
+#pragma unroll
+            for (int m = 0; m < C::TM; ++m)
+                f.b[h][m] = *reinterpret_cast<const bf16x8 *>(
+                    sx + (wm * C::WTM + m * 16 + lrow) * BK + chunk);
+        }
+    }
+    __device__ __forceinline__ void mfmas(const Frags &f) {  // K-steps in ascending order
+#pragma unroll
+        for (int h = 0; h < C::KH; ++h)
+#pragma unroll
+            for (int m = 0; m < C::TM; ++m)
+#pragma unroll
+                for (int t = 0; t < C::TN; ++t)
+                    acc[t][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.a[h][t], f.b[h][m],
+                                                                        acc[t][m], 0, 0, 0);
+    }
+
+    template <class W>
+    __device__ __forceinline__ void loop_a(bool stored, W) {
+        Frags f;
+        load_frags(f, 0);
+        for (int k = 0; k < nk; ++k) {
+            // compute phase: stage k
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_setprio(1);
+            if constexpr (W::value) mfmas(f);
+            __builtin_amdgcn_s_setprio(0);
+            // stage k+1 landed before the barrier; this wave's requests for
+            // stages k+2 .. k+NS-2 (and, older than those from the loop
+            // itself, the previous tile's stores) may stay in flight
+            if (stored && k <= NS - 3 && k + NS - 1 <= nk)
+                wait_vmcnt<(NS - 3) * C::LPS_A + C::STORES>();
+            else if (k + NS - 1 <= nk)
+                wait_vmcnt<(NS - 3) * C::LPS_A>();
+            else
+                wait_vmcnt<0>();
+            __builtin_amdgcn_s_barrier();
+            // memory phase: this wave's share of stage k+NS-1, fragments of
+            // stage k+1 (stale but in bounds past the end)
+            if (k + NS - 1 < nk) issue(k + NS - 1, nxa{});
+            load_frags(f, k + 1);
+            __builtin_amdgcn_s_barrier();
+        }
+    }
+    template <class W>
+    __device__ __forceinline__ void loop_b(bool stored, W) {
+        Frags f;
+        for (int k = 0; k < nk; ++k) {
+            // memory phase: this wave's share of stage k+NS-1, fragments of stage k
+            if (k + NS - 1 < nk) issue(k + NS - 1, nxb{});
+            load_frags(f, k);
+            // stage k+1 landed; this wave's requests for stages k+2 ..
+            // k+NS-1 (the last just issued) may stay in flight
+            if (stored && k <= NS - 3 && k + NS <= nk)
+                wait_vmcnt<(NS - 2) * C::LPS_B + C::STORES>();
+            else if (k + NS <= nk)
+                wait_vmcnt<(NS - 2) * C::LPS_B>();
+            else if (NS > 3 && k + NS == nk + 1 && k > NS - 3)
+                wait_vmcnt<(NS - 3) * C::LPS_B>();
+            else
+                wait_vmcnt<0>();
+            __builtin_amdgcn_s_barrier();
+            // compute phase: stage k
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_setprio(1);
+            if constexpr (W::value) mfmas(f);
+            __builtin_amdgcn_s_setprio(0);
+            __builtin_amdgcn_s_barrier();
+        }
+    }
+
+    __device__ __forceinline__ void store_piece(const TileArgs &a) {
+        tile_store_piece<C>(acc, wave, a);
+    }
+    __device__ __forceinline__ void epilogue(const TileArgs &a) {
+        tile_epilogue<MODE, C>(acc, smem, wave, a);
+    }
+};
 
 // Tile order inside one expert: super-columns of GROUP_N n-tiles, walked
 // row by row, so consecutive tiles share token rows and weight rows.
@@ -641,34 +531,17 @@ __device__ __forceinline__ void decode_tile(int tau, int MT, int NT, int &mt, in
     nt = sc * GROUP_N + (r - mt * width);
 }
 
-// Tile policies shared by the two schedulers.
-template <int MODE, int BN_, int BM_, int BK, int NS>
-struct FourWave {
-    using C = Cfg<MODE, BN_, BM_, BK, NS>;
-    static constexpr int THREADS = NTHREADS;
-    static constexpr int BM = BM_;
-    static constexpr int BNOUT = C::BNOUT;
-    static constexpr int LDS_ELEMS = NS * C::STAGE;
-    static constexpr int KSTEP = BK;
-    static constexpr bool CAN_SPLIT = false;  // covers the whole K range only
-    static constexpr int PART_ELEMS = 0;
-    static __device__ __forceinline__ void run(const TileArgs &a, bf16_t *smem) {
-        run_tile<MODE, BN_, BM_, BK, NS>(a, smem);
-    }
-};
+// Tile policy shared by the two schedulers.
 template <int MODE, int BM_>
 struct PingPong {
     using C = PPCfg<MODE, BM_>;  // also read by split_fixup_kernel
-    static constexpr int THREADS = PP_THREADS;
+    using Tile = PPTile<MODE, BM_>;
+    static constexpr int THREADS = 64 * C::WAVES;
     static constexpr int BM = C::BM;
     static constexpr int BNOUT = C::BNOUT;
     static constexpr int LDS_ELEMS = C::LDS_ELEMS;
     static constexpr int KSTEP = C::BK;
-    static constexpr bool CAN_SPLIT = true;
     static constexpr int PART_ELEMS = C::PART_ELEMS;
-    static __device__ __forceinline__ void run(const TileArgs &a, bf16_t *smem) {
-        run_tile_pp<MODE, BM_>(a, smem);
-    }
 };
 
 template <int MODE, class TP>
@@ -699,13 +572,15 @@ __global__ __launch_bounds__(TP::THREADS) void dense_kernel(const bf16_t *__rest
     a.nks = K / TP::KSTEP;
     a.ldo = ldo;
     a.part = nullptr;
-    a.piece = 0;
-    a.npieces = 1;
     if (MODE == 0)
         a.out = reinterpret_cast<bf16_t *>(out) + m0 * ldo + n0;
     else
         a.out = reinterpret_cast<float *>(out) + m0 * ldo + n0;
-    TP::run(a, smem);
+    typename TP::Tile tile(smem);
+    tile.bind(a);
+    tile.prologue();
+    tile.kloop(TP::Tile::NOTHING);
+    tile.epilogue(a);
 }
 
 template <int MODE, class TP>
@@ -741,7 +616,7 @@ __global__ __launch_bounds__(TP::THREADS) void group_kernel(
         if (tid < kMaxExperts) s_pre[tid + 1] += v;
         __syncthreads();
     }
-    const int total = s_pre[e_count];
+    const int total = __builtin_amdgcn_readfirstlane(s_pre[e_count]);
 
     const int G = gridDim.x;  // multiple of NXCD
     const int slot = (blockIdx.x % NXCD) * (G / NXCD) + blockIdx.x / NXCD;
@@ -773,10 +648,11 @@ __global__ __launch_bounds__(TP::THREADS) void group_kernel(
     const int rem = total - full;
     const int64_t W = (int64_t)rem * nk;
     int S = 1, P = 0;
-    if (TP::CAN_SPLIT && parts != nullptr && rem > 0 && rem <= kSplitMaxTail) {
+    if (parts != nullptr && rem > 0 && rem <= kSplitMaxTail) {
         if (full == 0 && 2 * rem > G && BM >= 192) {
             // mean valid rows per tile: all rows over the m-tiles
-            const int64_t rows_all = s_off[e_count] - s_off[0];
+            const int64_t rows_all =
+                __builtin_amdgcn_readfirstlane(s_off[e_count] - s_off[0]);
             if (2 * rows_all * NT <= (int64_t)BM * total) {
                 P = (int)min<int64_t>(min(G, kSplitSlots - rem), W / kSplitMinStagesAlone);
                 if (4 * rem > 3 * P) P = 0;
@@ -798,20 +674,23 @@ __global__ __launch_bounds__(TP::THREADS) void group_kernel(
     // tile tau over K stages [k0, k0 + nks); part: the slot of its partial
     // sums (NULL: the whole K range, outputs written); j >= 0: the tail tile
     // whose record this call writes (the call that starts at stage 0)
-    auto run_tau = [&](int tau, int k0, int nks, float *part, int j) {
-        // expert: last e with s_pre[e] <= tau
+    auto tile_args = [&](int tau, int k0, int nks, float *part, int j) {
+        // expert: last e with s_pre[e] <= tau (LDS values as scalars: the
+        // tile's addresses then stay out of the vector registers)
+        auto lds = [](const int &v) { return __builtin_amdgcn_readfirstlane(v); };
         int lo = 0, hi = e_count - 1;
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
-            if (s_pre[mid] <= tau) lo = mid; else hi = mid - 1;
+            if (lds(s_pre[mid]) <= tau) lo = mid; else hi = mid - 1;
         }
         const int e = lo;
-        const int cnt = s_off[e + 1] - s_off[e];
+        const int row0 = lds(s_off[e]);
+        const int cnt = lds(s_off[e + 1]) - row0;
         const int MT = (cnt + BM - 1) / BM;
         int mt, nt;
-        decode_tile(tau - s_pre[e], MT, NT, mt, nt);
+        decode_tile(tau - lds(s_pre[e]), MT, NT, mt, nt);
         const int64_t n0 = (int64_t)nt * TP::BNOUT;
-        const int64_t r0 = (int64_t)s_off[e] + (int64_t)mt * BM;
+        const int64_t r0 = (int64_t)row0 + (int64_t)mt * BM;
         TileArgs a;
         const int64_t woffe = (int64_t)(e_first + e) * wstride;
         a.w0 = w0s + woffe + n0 * K;
@@ -830,8 +709,6 @@ __global__ __launch_bounds__(TP::THREADS) void group_kernel(
         else
             a.out = reinterpret_cast<float *>(out) + r0 * ldo + n0;
         a.part = part;
-        a.piece = 0;
-        a.npieces = part != nullptr ? 2 : 1;
         if (j >= 0 && tid == 0) {
             int32_t *md = split_meta + 4 + 4 * j;
             md[0] = (int32_t)r0;
@@ -839,34 +716,67 @@ __global__ __launch_bounds__(TP::THREADS) void group_kernel(
             md[2] = a.m_valid;
             md[3] = a.n_valid;
         }
-        TP::run(a, smem);
+        return a;
     };
-
-    if (P > 0) {
-        // stream-K tail (full == 0): at most one unit per workgroup
-        if (slot < P) {
-            const int64_t g0 = (int64_t)slot * W / P, g1 = (int64_t)(slot + 1) * W / P;
-            for (int j = (int)(g0 / nk); (int64_t)j * nk < g1; ++j) {
-                const int64_t a0 = max<int64_t>(g0, (int64_t)j * nk);
-                const int64_t a1 = min<int64_t>(g1, (int64_t)(j + 1) * nk);
-                run_tau(j, (int)(a0 - (int64_t)j * nk), (int)(a1 - a0),
-                        parts + (size_t)(slot + j) * TP::PART_ELEMS, a0 == (int64_t)j * nk ? j : -1);
-            }
-        }
-        return;
-    }
+    // The workgroup's work, in order: `u` counts its whole tiles and equal
+    // pieces (slot, slot + G, ..: at most one piece, the last); in the
+    // stream-K form the stages [g, g1) of its unit, one tile's segment at a
+    // time.
     const int end = S > 1 ? full : total;
-    const int units = S > 1 ? full + rem * S : total;
-    for (int u = slot; u < units; u += G) {
+    const int units = P > 0 ? 0 : S > 1 ? full + rem * S : total;
+    int u = slot;
+    int64_t g = 0, g1 = 0;
+    if (P > 0 && slot < P) {
+        g = (int64_t)slot * W / P;
+        g1 = (int64_t)(slot + 1) * W / P;
+    }
+    auto take = [&](TileArgs &a) {
+        if (P > 0) {
+            if (g >= g1) return false;
+            const int j = (int)(g / nk);
+            const int64_t t0 = (int64_t)j * nk, stop = min<int64_t>(g1, t0 + nk);
+            a = tile_args(j, (int)(g - t0), (int)(stop - g),
+                          parts + (size_t)(slot + j) * TP::PART_ELEMS, g == t0 ? j : -1);
+            g = stop;
+            return true;
+        }
+        if (u >= units) return false;
         if (u < end) {
-            run_tau(u, 0, nk, nullptr, -1);
+            a = tile_args(u, 0, nk, nullptr, -1);
         } else {
             // piece p of S covers stages [p*nk/S, (p+1)*nk/S)
             const int j = (u - full) / S, piece = (u - full) % S;
             const int k0 = piece * nk / S;
-            run_tau(full + j, k0, (piece + 1) * nk / S - k0,
-                    parts + (size_t)(j * S + piece) * TP::PART_ELEMS, piece == 0 ? j : -1);
+            a = tile_args(full + j, k0, (piece + 1) * nk / S - k0,
+                          parts + (size_t)(j * S + piece) * TP::PART_ELEMS, piece == 0 ? j : -1);
         }
+        u += G;
+        return true;
+    };
+    using Tile = typename TP::Tile;
+    Tile tile(smem);
+    TileArgs a;
+    if (!take(a)) return;
+    tile.bind(a);
+    tile.prologue();
+    typename Tile::After after = Tile::NOTHING;
+    while (true) {
+        tile.kloop(after);
+        TileArgs next;
+        const bool more = take(next);
+        if (more) {
+            tile.bind(next);
+            tile.prologue();
+        }
+        if (a.part != nullptr) {
+            tile.store_piece(a);
+            after = Tile::PIECE;
+        } else {
+            tile.epilogue(a);
+            after = Tile::STORES;
+        }
+        if (!more) break;
+        a = next;
     }
 }
 
@@ -934,9 +844,9 @@ __global__ __launch_bounds__(256) void split_fixup_kernel(const float *__restric
     const int64_t W = (int64_t)ntail * nk;
     const int p = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
-    for (int unit = blockIdx.x; unit < ntail * 8; unit += gridDim.x) {
-        const int j = unit / 8;
-        const int wave = unit % 8;
+    for (int unit = blockIdx.x; unit < ntail * C::WAVES; unit += gridDim.x) {
+        const int j = unit / C::WAVES;
+        const int wave = unit % C::WAVES;
         // the tile's pieces sit in consecutive slots [first, first + S), in K order
         int first, S;
         if (S_eq > 0) {
@@ -978,16 +888,8 @@ __global__ __launch_bounds__(256) void split_fixup_kernel(const float *__restric
 // rows (fewest LDS bytes per MFMA) above 256; a dense launch knows its
 // expert's rows and takes the height whose tile count fills the grid best
 // (dense_tile_rows).
-#ifndef MOE_GEMM_PINGPONG
-#define MOE_GEMM_PINGPONG 1
-#endif
-#if MOE_GEMM_PINGPONG
 constexpr int kTokenTile = 320;
 template <int MODE, int BM = kTokenTile> using TileOf = PingPong<MODE, BM>;
-#else
-constexpr int kTokenTile = 256;
-template <int MODE, int BM = kTokenTile> using TileOf = FourWave<MODE, 256, 256, 32, 4>;
-#endif
 template <int MODE> using GroupTile = TileOf<MODE>;
 
 // ---------------------------------------------------------------------------
@@ -1204,14 +1106,10 @@ int round_grid(int64_t tiles) { return (int)(((tiles + NXCD - 1) / NXCD) * NXCD)
 template <int MODE, class TP>
 hipError_t launch_split_fixup(int grid, const float *parts, const int32_t *meta, void *out,
                               int64_t ldo, hipStream_t s) {
-    if constexpr (!TP::CAN_SPLIT) {
-        return hipSuccess;
-    } else {
-        const int max_tail = std::min(grid, kSplitMaxTail);
-        const int blocks = std::min(max_tail * 8, device_cu_count());
-        split_fixup_kernel<MODE, TP><<<blocks, 256, 0, s>>>(parts, meta, out, ldo);
-        return hipGetLastError();
-    }
+    const int max_tail = std::min(grid, kSplitMaxTail);
+    const int blocks = std::min(max_tail * TP::C::WAVES, device_cu_count());
+    split_fixup_kernel<MODE, TP><<<blocks, 256, 0, s>>>(parts, meta, out, ldo);
+    return hipGetLastError();
 }
 
 template <int MODE, class TP>
@@ -1238,16 +1136,12 @@ hipError_t group_launch_bm(int bm, const int32_t *offsets, int e_first, int e_co
     return group_launch<MODE, TileOf<MODE, BMV>>(offsets, e_first, e_count, x, row_map,       \
                                                  slot_div, w0s, w1s, wstride, N, K, out, ldo, \
                                                  grid, parts, split_meta, rows_one, s)
-#if MOE_GEMM_PINGPONG
     switch (bm) {
         case 128: MOE_GROUP_LAUNCH(128);
         case 192: MOE_GROUP_LAUNCH(192);
         case 256: MOE_GROUP_LAUNCH(256);
         default: MOE_GROUP_LAUNCH(320);
     }
-#else
-    MOE_GROUP_LAUNCH(256);
-#endif
 #undef MOE_GROUP_LAUNCH
 }
 
@@ -1264,16 +1158,12 @@ hipError_t dense_launch(int64_t rows, const bf16_t *x, const bf16_t *w0, const b
 template <int MODE>
 hipError_t dense_launch_bm(int bm, int64_t rows, const bf16_t *x, const bf16_t *w0,
                            const bf16_t *w1, int N, int K, void *out, int64_t ldo, hipStream_t s) {
-#if MOE_GEMM_PINGPONG
     switch (bm) {
         case 128: return dense_launch<MODE, TileOf<MODE, 128>>(rows, x, w0, w1, N, K, out, ldo, s);
         case 192: return dense_launch<MODE, TileOf<MODE, 192>>(rows, x, w0, w1, N, K, out, ldo, s);
         case 256: return dense_launch<MODE, TileOf<MODE, 256>>(rows, x, w0, w1, N, K, out, ldo, s);
         default: return dense_launch<MODE, TileOf<MODE, 320>>(rows, x, w0, w1, N, K, out, ldo, s);
     }
-#else
-    return dense_launch<MODE, TileOf<MODE>>(rows, x, w0, w1, N, K, out, ldo, s);
-#endif
 }
 
 // ---- launch cost model (host) ---------------------------------------------
@@ -1359,7 +1249,6 @@ double ffn_expert_us(int bm, int64_t rows, int H, int I, int grid, bool split) {
 }
 
 int dense_tile_rows(int64_t rows, int H, int I, int grid, bool split) {
-#if MOE_GEMM_PINGPONG
     int best = kTokenTile;
     double best_us = 0.0;
     for (const TileCost &c : kTileCosts) {
@@ -1370,19 +1259,14 @@ int dense_tile_rows(int64_t rows, int H, int I, int grid, bool split) {
         }
     }
     return best;
-#else
-    return kTokenTile;
-#endif
 }
 
 int group_tile_rows(int64_t max_rows) {
-#if MOE_GEMM_PINGPONG
     // below the tallest tile, the smallest height that still holds every
     // expert's rows in one tile: fewer padded rows, never more tiles
     if (max_rows <= 128) return 128;
     if (max_rows <= 192) return 192;
     if (max_rows <= 256) return 256;
-#endif
     (void)max_rows;
     return kTokenTile;
 }
@@ -1435,7 +1319,6 @@ void expected_mtiles(int64_t tokens, double p, int64_t cap, double out[4]) {
 int group_launch_rows(int64_t max_rows, const int32_t *rows, int n_experts, int64_t tokens,
                       double p, int H, int I, int grid, bool split) {
     const int cap = group_tile_rows(max_rows);
-#if MOE_GEMM_PINGPONG
     if (n_experts <= 0 || cap == kTileHeights[0]) return cap;
     double mt[4];
     if (rows == nullptr) expected_mtiles(tokens, p, max_rows, mt);
@@ -1461,18 +1344,10 @@ int group_launch_rows(int64_t max_rows, const int32_t *rows, int n_experts, int6
     }
     // another height only for a predicted gain above the model's error
     return us[best] < (1.0 - kGroupRowsMinGain) * us[icap] ? kTileHeights[best] : cap;
-#else
-    (void)rows, (void)n_experts, (void)tokens, (void)p, (void)H, (void)I, (void)grid, (void)split;
-    return cap;
-#endif
 }
 
 bool valid_tile_rows(int bm) {
-#if MOE_GEMM_PINGPONG
     return bm == 128 || bm == 192 || bm == 256 || bm == 320;
-#else
-    return bm == kTokenTile;
-#endif
 }
 
 hipError_t launch_dense_gateup(int64_t rows, int H, int I, const bf16_t *x, const bf16_t *w_gate,

@@ -1,16 +1,13 @@
 // Device helpers the router kernels share: cross-lane maxima and sums, top-k
-// selection with softmax weights, and the LDS-DMA request.
+// selection with softmax weights.
 #pragma once
 
 #include <type_traits>
 
-#include "common.h"
+#include "lds_dma.h"
 
 namespace moe {
 namespace {
-
-typedef __attribute__((address_space(3))) void lds_void_t;
-typedef __attribute__((address_space(1))) void gbl_void_t;
 
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp32(uint32_t v) {
@@ -184,22 +181,6 @@ __device__ __forceinline__ void select_token(const float *zrow, int64_t t, int E
     const float *const z[1] = {zrow};
     const int64_t tt[1] = {t};
     select_tokens<1>(z, tt, t + 1, E, k, renorm, lane, ids, wout);
-}
-
-// One 16-byte-per-lane LDS-DMA request (lane l's bytes land at lds_addr +
-// 16 l; lds_addr must be the same in every lane), written out so that the
-// compiler does not see an LDS write in
-// flight: it would put a full vmcnt(0) in front of every later LDS read,
-// which makes the next chunk's loads finish before the current chunk is
-// multiplied.  The kernel's own vmcnt wait and barrier order the data.
-__device__ __forceinline__ void dma16_to_lds(const void *gptr, uint32_t lds_addr) {
-    // the LDS address goes in through an "{m0}" operand, so the compiler
-    // itself writes m0 (and knows it does); the s_nop separates that write
-    // from the load that reads it
-    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-                 :
-                 : "v"(gptr), "{m0}"(__builtin_amdgcn_readfirstlane(lds_addr))
-                 : "memory");
 }
 
 // Calls f(integral_constant<int, I>) for I = B .. N - 1.

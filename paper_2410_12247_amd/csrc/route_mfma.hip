@@ -72,22 +72,6 @@ struct Cfg {
     static_assert(LDS <= 160 * 1024, "LDS");
 };
 
-// dma16_to_lds through a buffer resource: lane l's 16 bytes at base + voff +
-// soff land at lds_addr + 16 l.
-__device__ __forceinline__ void buf16_to_lds(const u32x4 &rsrc, uint32_t voff, uint32_t soff,
-                                             uint32_t lds_addr) {
-    asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
-                 :
-                 : "v"(voff), "s"(rsrc), "s"(soff), "{m0}"(lds_addr)
-                 : "memory");
-}
-__device__ __forceinline__ u32x4 buf_rsrc(const void *p) {
-    const uint64_t b = (uint64_t)(uintptr_t)p;
-    return u32x4{(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)b),
-                 (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(b >> 32)), 0xFFFFFFFFu,
-                 0x00020000u};
-}
-
 // acc[m][n]: lane l gets token 16 m + l % 16, experts 16 n + 4 (l / 16) .. + 3
 template <int TT, int TE, int TW, int EW, int NS>
 __device__ __forceinline__ void logits(char *lds, floatx4 (&acc)[TT][TE],
