@@ -30,8 +30,9 @@
  *   moe_ffn_dense) every expert-GEMM output is one pass over K, so the bits
  *   are also the same for any pipeline number, stage kind, CU budget and
  *   either GEMM kind.  Without it the grouped GEMM may cut the tiles of its
- *   last, partial round into K pieces summed in a fixed order, which moves
- *   the last bits of those outputs with the launch's tile count.
+ *   last, partial round, or every tile of a launch of few rows per expert,
+ *   into K pieces summed in a fixed order, which moves the last bits of
+ *   those outputs with the launch's tile count.
  */
 #ifndef MOE_H
 #define MOE_H

@@ -243,10 +243,8 @@ moe_status moe_ffn_group(const moe_dims *dims, int32_t e_first, int32_t e_count,
                                 act, grid, nullptr, nullptr, bm, s));
     // decode-sized experts with enough tiles: the skinny down tile
     const int64_t active = std::min<int64_t>(e_count, dims->tokens * dims->top_k);
-    const int sk = skinny_down_rows(dims->tokens, active, dims->hidden);
-    if (sk > 0)
-        MOE_HIP(launch_skinny_down(*dims, e_first, e_count, offsets, act, w_down, y_perm, sk,
-                                   active, s));
+    if (skinny_down_fits(dims->tokens, active, dims->hidden, dims->inter))
+        MOE_HIP(launch_skinny_down(*dims, e_first, e_count, offsets, act, w_down, y_perm, s));
     else
         MOE_HIP(launch_group_down(*dims, e_first, e_count, offsets, act, w_down, y_perm, grid,
                                   nullptr, nullptr, bm, s));

@@ -207,18 +207,27 @@ constexpr double kGroupRowsMinGain = 0.05;
 int group_launch_rows(int64_t max_rows, const int32_t *rows, int n_experts, int64_t tokens,
                       double p, int H, int I, int grid, bool split);
 // Skinny down GEMM for decode-sized grouped launches: one wave per tile of
-// 64 output columns by an expert's rows (at most 64) over the whole K
-// range, no K split (the same bits as every other tile height in exact
-// order).  skinny_down_rows gives the tile's rows (16, 32 or 64) for a
-// launch whose experts have at most max_rows rows, of which at most
-// active_experts have any, with N output columns; 0 where the skinny tile
-// does not apply: more rows, or fewer than two tiles per compute unit (the
-// general tile's K split then keeps more loads in flight).
+// 64 output columns by an expert's rows (at most 64) over the whole K range,
+// no K split (the same bits as every other tile height in exact order).  It
+// applies from two tiles per compute unit, counting the experts that may
+// have rows (below, the other forms' K splits keep more loads in flight).
 constexpr int64_t kSkinnyMaxRows = 64;
-int skinny_down_rows(int64_t max_rows, int64_t active_experts, int N);
+bool skinny_down_fits(int64_t max_rows, int64_t active_experts, int N, int K);
 hipError_t launch_skinny_down(const moe_dims &d, int e_first, int e_count,
                               const int32_t *offsets, const bf16_t *act, const bf16_t *w_down,
-                              float *y_perm, int bm, int64_t active_experts, hipStream_t s);
+                              float *y_perm, hipStream_t s);
+// The GEMMs of launches whose experts have at most kStreamMaxRows rows,
+// streaming the weights once with K split over the waves of a workgroup (not
+// the bits of exact order).
+constexpr int64_t kStreamMaxRows = 16;
+bool stream_fits(int64_t max_rows, int H, int I);
+hipError_t launch_stream_gateup(const moe_dims &d, int e_first, int e_count,
+                                const int32_t *offsets, const bf16_t *x, const int32_t *row_map,
+                                const bf16_t *w_gate, const bf16_t *w_up, bf16_t *act,
+                                hipStream_t s);
+hipError_t launch_stream_down(const moe_dims &d, int e_first, int e_count,
+                              const int32_t *offsets, const bf16_t *act, const bf16_t *w_down,
+                              float *y, hipStream_t s);
 bool valid_tile_rows(int bm);
 
 }  // namespace moe

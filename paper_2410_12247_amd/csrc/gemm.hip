@@ -894,15 +894,18 @@ template <int MODE> using GroupTile = TileOf<MODE>;
 
 // ---------------------------------------------------------------------------
 // Skinny down tile for decode-sized grouped launches: every expert of the
-// launch has at most BM (16, 32 or 64) rows, so its down GEMM is one row of
-// tiles that streams the expert's weights once.  A workgroup is one wave
-// and owns SK_BN output columns (weight rows) by the expert's rows over the
-// whole K range: no K split, no fixup.  Weight and act rows stream through
-// a ring of LDS stages of SK_BK K by LDS-DMA, all but one stage ahead, the
-// 16-byte chunks of each row XOR-placed as in the ping-pong tile.  The ring depth is chosen per
-// launch (dynamic LDS): the deepest with which every tile of the launch is
-// resident at once (a second, partial round of tiles would take as long as
-// the first).  The MFMA (16x16x32 bf16, the weight fragment as the A
+// launch has at most 64 rows, so its down GEMM is one row of tiles that
+// streams the expert's weights once.  A workgroup is one wave and owns SK_BN
+// output columns (weight rows) by the expert's rows over the whole K range:
+// no K split, no fixup.  The height (16, 32 or 64 rows) is the workgroup's
+// own, from its expert's row count: a launch of 61 tokens over 160 experts
+// has one or two experts above 16 rows, and a height taken from the upper
+// bound would make every other tile read and multiply padding (us, one
+// height for the launch -> per expert: DeepSeekV2 61 tokens 62 -> 51, DBRX 64
+// 50.9 -> 49.0, 64 tokens over 64 experts of 2048 x 1024 20.5 -> 19.3).
+// Weight and act rows stream through a ring of LDS stages of SK_BK K by
+// LDS-DMA, all but one stage ahead, as many stages as 64 KB of LDS hold, the
+// 16-byte chunks of each row XOR-placed as in the ping-pong tile.  The MFMA (16x16x32 bf16, the weight fragment as the A
 // operand, K ascending from 0) and the fragment contents are the ping-pong
 // tile's, so the outputs carry the same bits as every other tile height in
 // exact order.  The fragment reads and their wait are one assembly block:
@@ -918,14 +921,22 @@ constexpr int SK_NS_MAX = 16;             // ring stages at most
 constexpr size_t SK_LDS_MAX = 64 * 1024;  // dynamic LDS of one workgroup at most
 
 // stages a wave can keep ahead: vmcnt counts at most 63 requests
-constexpr int sk_ahead_max(int lps) { return std::min(SK_NS_MAX - 1, 63 / lps); }
+__host__ __device__ constexpr int sk_ahead_max(int lps) {
+    return SK_NS_MAX - 1 < 63 / lps ? SK_NS_MAX - 1 : 63 / lps;
+}
 // LDS-DMA requests per stage (64 lanes x 16 bytes each)
-constexpr int sk_lps(int bm, int bk) { return (SK_BN + bm) * bk * 2 / 1024; }
+__host__ __device__ constexpr int sk_lps(int bm, int bk) { return (SK_BN + bm) * bk * 2 / 1024; }
 
 // LDS bytes of a workgroup with a ring of ns stages of bk K: the ring plus
 // room for the act-fragment reads a tile of fewer than 64 rows does not use
-constexpr size_t sk_lds_bytes(int bm, int bk, int ns) {
+__host__ __device__ constexpr size_t sk_lds_bytes(int bm, int bk, int ns) {
     return (size_t)ns * (SK_BN + bm) * bk * 2 + (size_t)(4 - bm / 16) * 16 * bk * 2;
+}
+// stages of a tile of bm rows in SK_LDS_MAX, as many as vmcnt can count
+__host__ __device__ constexpr int sk_ring(int bm, int bk) {
+    int ns = sk_ahead_max(sk_lps(bm, bk)) + 1;
+    while (sk_lds_bytes(bm, bk, ns) > SK_LDS_MAX) --ns;
+    return ns;
 }
 
 // one K-step's fragments: 4 weight fragments from wa, 4 act fragments from
@@ -959,16 +970,13 @@ __device__ __forceinline__ void sk_wait(int n) {
     }
 }
 
-// y[r0 + r][n0 .. n0 + 63] = w_down[e_first + e][n0 ..] . act[r0 + r] for
-// the r < rows of expert e (offsets indexed by e_first + e, as in the other
-// launches); grid = e_count * (N / SK_BN), ns ring stages of BK K.
+// One tile: y columns n0 .. n0 + 63 of the `rows` <= BM rows from r0 on; w:
+// the expert's weights; ns ring stages of BK K.
 template <int BM, int BK>
-__global__ __launch_bounds__(64) void skinny_down_kernel(const int32_t *__restrict__ offsets,
-                                                         int e_first, int e_count,
-                                                         const bf16_t *__restrict__ act,
-                                                         const bf16_t *__restrict__ w,
-                                                         int64_t wstride, int N, int K,
-                                                         float *__restrict__ y, int ns) {
+__device__ __forceinline__ void skinny_tile(bf16_t *smem, int ns, int r0, int rows, int n0,
+                                            const bf16_t *__restrict__ act,
+                                            const bf16_t *__restrict__ w, int N, int K,
+                                            float *__restrict__ y) {
     constexpr int TN = SK_BN / 16, TM = BM / 16;
     static_assert(TM <= 4, "at most 4 act fragments per K-step");
     static_assert(BK == 32 || BK == 64, "16-byte chunks: 4 or 8 per LDS row");
@@ -980,18 +988,7 @@ __global__ __launch_bounds__(64) void skinny_down_kernel(const int32_t *__restri
     constexpr int STAGE = (SK_BN + BM) * BK;  // bf16 elements
     constexpr int F = 16 * BK * 2;            // bytes of 16 LDS rows
     constexpr int KH = BK / 32;               // MFMA K-steps per stage
-    // ring of ns stages (2 <= ns <= sk_ahead_max(LPS) + 1), sk_lds_bytes
-    extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
-
-    const int NT = N / SK_BN;
-    const int e = blockIdx.x / NT;
-    const int nt = blockIdx.x - e * NT;
-    if (e >= e_count) return;
-    const int r0 = offsets[e_first + e];
-    const int rows = offsets[e_first + e + 1] - r0;  // <= BM (the launcher's bound)
-    if (rows <= 0) return;
     const int lane = threadIdx.x;
-    const int64_t n0 = (int64_t)nt * SK_BN;
 
     // LDS-DMA sources: lane i fetches row (i / CPR) of an RPI-row request,
     // the 16-byte chunk (i % CPR) ^ swz(row) of the stage's BK K, into
@@ -999,28 +996,25 @@ __global__ __launch_bounds__(64) void skinny_down_kernel(const int32_t *__restri
     const int drow = lane / CPR;
     const int dchunk = ((lane % CPR) ^ swz<BK>(drow)) * 8;
     const bf16_t *src[LPS];
-    const bf16_t *we = w + (int64_t)(e_first + e) * wstride;
 #pragma unroll
-    for (int i = 0; i < WI; ++i) src[i] = we + (n0 + i * RPI + drow) * K + dchunk;
+    for (int i = 0; i < WI; ++i) src[i] = w + (int64_t)(n0 + i * RPI + drow) * K + dchunk;
 #pragma unroll
     for (int i = 0; i < XI; ++i) {
         const int j = min(i * RPI + drow, rows - 1);  // rows past the expert's: repeats
         src[WI + i] = act + (int64_t)(r0 + j) * K + dchunk;
     }
     const int nk = K / BK;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void_t *)smem;
     auto issue = [&](int kt, int slot) {
-        bf16_t *sb = smem + slot * STAGE;
 #pragma unroll
         for (int i = 0; i < LPS; ++i)
-            __builtin_amdgcn_global_load_lds((gbl_void_t *)(src[i] + kt * BK),
-                                             (lds_void_t *)(sb + i * RPI * BK), 16, 0, 0);
+            dma16_to_lds(src[i] + kt * BK, lds0 + (slot * STAGE + i * RPI * BK) * 2);
     };
 
     // fragment addresses in ring slot 0, K-step h of the stage: weight row
     // t * 16 + lrow and act row m * 16 + lrow, the chunk holding K
     // 32 h + 8 (lane / 16) .. + 7
     const int lrow = lane & 15;
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void_t *)smem;
     uint32_t wa0[KH], xa0[KH];
 #pragma unroll
     for (int h = 0; h < KH; ++h) {
@@ -1072,29 +1066,35 @@ __global__ __launch_bounds__(64) void skinny_down_kernel(const int32_t *__restri
     }
 }
 
-// Ring depth of a launch of `tiles` non-empty tiles: the deepest ring (at
-// most sk_ahead_max + 1 stages, SK_LDS_MAX bytes) with which the tiles of a
-// compute unit all fit its LDS at once, and at least 4 stages.
-int sk_ring(int bm, int bk, int64_t tiles) {
-    const int cus = device_cu_count();
-    const int64_t per_cu = std::max<int64_t>(1, (tiles + cus - 1) / cus);
-    const size_t cap = std::min<size_t>(SK_LDS_MAX, (size_t)(160 * 1024) / per_cu);
-    int ns = sk_ahead_max(sk_lps(bm, bk)) + 1;
-    while (ns > 4 && sk_lds_bytes(bm, bk, ns) > cap) --ns;
-    return ns;
-}
-
-template <int BM, int BK>
-hipError_t skinny_down_launch(unsigned blocks, int64_t tiles, const int32_t *offsets,
-                              int e_first, int e_count, const bf16_t *act, const bf16_t *w,
-                              int64_t wstride, int N, int K, float *y, hipStream_t s) {
-    if (K % BK) return hipErrorInvalidValue;
-    const int ns = sk_ring(BM, BK, tiles);
-    if (ns < 2 || ns - 1 > sk_ahead_max(sk_lps(BM, BK)) || sk_lds_bytes(BM, BK, ns) > SK_LDS_MAX)
-        return hipErrorInvalidValue;
-    skinny_down_kernel<BM, BK><<<blocks, 64, sk_lds_bytes(BM, BK, ns), s>>>(
-        offsets, e_first, e_count, act, w, wstride, N, K, y, ns);
-    return hipGetLastError();
+// y[r0 + r][n0 .. n0 + 63] = w_down[e_first + e][n0 ..] . act[r0 + r] for
+// the r < rows of expert e (offsets indexed by e_first + e, as in the other
+// launches); grid = e_count * (N / SK_BN).  The expert's rows, read on the
+// device, pick the tile's height (every expert's may be far below the
+// launch's bound, the tokens), and the ring takes what SK_LDS_MAX holds:
+// against one height for the launch, us, DeepSeekV2 61 tokens 62 -> 51, Zipf
+// 64 tokens 20.5 -> 19.3, DBRX 64 tokens 50.9 -> 49.0.
+template <int BK>
+__global__ __launch_bounds__(64) void skinny_down_kernel(const int32_t *__restrict__ offsets,
+                                                         int e_first, int e_count,
+                                                         const bf16_t *__restrict__ act,
+                                                         const bf16_t *__restrict__ w,
+                                                         int64_t wstride, int N, int K,
+                                                         float *__restrict__ y) {
+    extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
+    const int NT = N / SK_BN;
+    const int e = blockIdx.x / NT;
+    const int n0 = (blockIdx.x - e * NT) * SK_BN;
+    if (e >= e_count) return;
+    const int r0 = __builtin_amdgcn_readfirstlane(offsets[e_first + e]);
+    const int rows = __builtin_amdgcn_readfirstlane(offsets[e_first + e + 1]) - r0;
+    if (rows <= 0) return;  // (rows <= 64: the launcher's bound)
+    const bf16_t *we = w + (int64_t)(e_first + e) * wstride;
+    if (rows <= 16)
+        skinny_tile<16, BK>(smem, sk_ring(16, BK), r0, rows, n0, act, we, N, K, y);
+    else if (rows <= 32)
+        skinny_tile<32, BK>(smem, sk_ring(32, BK), r0, rows, n0, act, we, N, K, y);
+    else
+        skinny_tile<64, BK>(smem, sk_ring(64, BK), r0, rows, n0, act, we, N, K, y);
 }
 
 int round_grid(int64_t tiles) { return (int)(((tiles + NXCD - 1) / NXCD) * NXCD); }
@@ -1393,35 +1393,21 @@ hipError_t launch_group_down(const moe_dims &d, int e_first, int e_count,
                               grid, parts, split_meta, (int)rows_one, s);
 }
 
-int skinny_down_rows(int64_t max_rows, int64_t active_experts, int N) {
-    if (max_rows > kSkinnyMaxRows || N % SK_BN) return 0;
-    if (active_experts * (N / SK_BN) < 2 * (int64_t)device_cu_count()) return 0;
-    return max_rows <= 16 ? 16 : max_rows <= 32 ? 32 : 64;
+bool skinny_down_fits(int64_t max_rows, int64_t active_experts, int N, int K) {
+    return max_rows <= kSkinnyMaxRows && N % SK_BN == 0 && K % SK_BK == 0 &&
+           active_experts * (N / SK_BN) >= 2 * (int64_t)device_cu_count();
 }
 
 hipError_t launch_skinny_down(const moe_dims &d, int e_first, int e_count,
                               const int32_t *offsets, const bf16_t *act, const bf16_t *w_down,
-                              float *y_perm, int bm, int64_t active_experts, hipStream_t s) {
+                              float *y_perm, hipStream_t s) {
     if (e_count <= 0) return hipSuccess;
     const int N = d.hidden, K = d.inter;
     if (N % SK_BN || K % SK_BK) return hipErrorInvalidValue;
-    const unsigned blocks = (unsigned)(e_count * (N / SK_BN));
-    const int64_t active = std::min<int64_t>(e_count, std::max<int64_t>(1, active_experts));
-    const int64_t tiles = active * (N / SK_BN);
-    const int64_t wstride = (int64_t)N * K;
-    switch (bm) {
-        case 16:
-            return skinny_down_launch<16, SK_BK>(blocks, tiles, offsets, e_first, e_count, act,
-                                                 w_down, wstride, N, K, y_perm, s);
-        case 32:
-            return skinny_down_launch<32, SK_BK>(blocks, tiles, offsets, e_first, e_count, act,
-                                                 w_down, wstride, N, K, y_perm, s);
-        case 64:
-            return skinny_down_launch<64, SK_BK>(blocks, tiles, offsets, e_first, e_count, act,
-                                                 w_down, wstride, N, K, y_perm, s);
-        default:
-            return hipErrorInvalidValue;
-    }
+    static_assert(sk_ring(64, SK_BK) >= 2 && sk_ring(16, SK_BK) >= 2, "ring depth");
+    skinny_down_kernel<SK_BK><<<(unsigned)(e_count * (N / SK_BN)), 64, SK_LDS_MAX, s>>>(
+        offsets, e_first, e_count, act, w_down, (int64_t)N * K, N, K, y_perm);
+    return hipGetLastError();
 }
 
 }  // namespace moe

@@ -68,3 +68,69 @@ def test_dense_tiles(rows, H, I):
     assert bool((y[rows] == 7.0).all()), "wrote past the last row"
     want, bound = reference(x, wg, wu, wd)
     assert bool(((y[:rows].double() - want).abs() <= bound).all())
+
+
+def test_skinny_heights_mixed():
+    """One decode launch whose experts have 0 to 64 rows: each expert's rows
+    pick the height of its down tiles."""
+    rows = [0, 1, 16, 17, 32, 33, 64]
+    H, I, E, R = 4736, 128, len(rows), sum(rows)  # 7 x 74 tiles: at least two per compute unit
+    rng = np.random.default_rng(5)
+    off = torch.from_numpy(np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)).to(dev())
+    x = ints(rng, R, H)
+    wg, wu, wd = ints(rng, E, I, H), ints(rng, E, I, H), ints(rng, E, H, I)
+    d = moe.dims(64, H, I, 8, 8, 0, E, True)
+    act = torch.zeros((R, I), dtype=torch.bfloat16, device=dev())
+    y = torch.full((R + 1, H), 7.0, device=dev())
+    moe.ffn_group(d, 0, E, off, x, wg, wu, wd, act, y[:R])
+    torch.cuda.synchronize()
+    assert bool((y[R] == 7.0).all()), "wrote past the last row"
+    for e in range(E):
+        r0, r1 = int(off[e]), int(off[e + 1])
+        want, bound = reference(x[r0:r1], wg[e], wu[e], wd[e])
+        assert bool(((y[r0:r1].double() - want).abs() <= bound).all()), f"expert of {rows[e]} rows"
+
+
+@pytest.mark.parametrize("T", [1, 2, 7, 16])
+@pytest.mark.parametrize("H,I", [
+    (64, 64),       # two K steps: most waves have none
+    (320, 192),     # ten and six steps over eight waves
+    (1344, 576),    # uneven pieces, more steps than are in flight
+    (576, 2112),    # the deep ring of the down GEMM
+])
+def test_stream_gemms(T, H, I):
+    """The forward of a few tokens without shared experts: both GEMMs stream
+    the weights with K cut over the waves.  Against 64-bit sums, repeated
+    calls and the no-allocation entry point bit for bit, and within the K
+    split's rounding of exact order."""
+    E, k, e0, EL = 8, 2, 1, 6
+    rng = np.random.default_rng(T + H)
+    x = torch.from_numpy(rng.standard_normal((T, H)).astype(np.float32)).to(dev(), torch.bfloat16)
+    wr = torch.from_numpy(rng.standard_normal((E, H)).astype(np.float32) * 0.05).to(dev())
+    w = lambda *s: torch.from_numpy(  # noqa: E731
+        rng.standard_normal(s).astype(np.float32) * 0.05).to(dev(), torch.bfloat16)
+    wg, wu, wd = w(EL, I, H), w(EL, I, H), w(EL, H, I)
+    d = moe.dims(T, H, I, E, k, e0, EL, True)
+    out = []
+    for o in (moe.opts(), moe.opts(), moe.opts(exact_order=True)):
+        b = moe.MoEBuffers(d, o)
+        out.append((b, b.run(x, wr, None, wg, wu, wd)))
+    y2 = torch.empty_like(out[0][1])
+    moe.forward_noalloc(d, moe.opts(), x, wr, None, wg, wu, wd, None, None, None, y2, None, None,
+                        None)
+    torch.cuda.synchronize()
+    b, y = out[0]
+    assert torch.equal(y, out[1][1]) and torch.equal(y, y2)
+    want, bound = torch.zeros(T, H, dtype=torch.float64, device=dev()), 0.0
+    for t in range(T):
+        for j in range(k):
+            e = int(b.topk_ids[t, j]) - e0
+            if 0 <= e < EL:
+                r, bd = reference(x[t:t + 1], wg[e], wu[e], wd[e])
+                want[t] += float(b.topk_w[t, j]) * r[0]
+                bound = max(bound, float(bd.max()))
+    # bf16 activations (reference's bound), doubled for the fp32 sums of
+    # non-integers, over at most k experts
+    assert float((y.double() - want).abs().max()) <= 2 * k * bound
+    scale = float(want.abs().max())
+    assert float((y - out[2][1]).abs().max()) <= 2e-2 * scale
