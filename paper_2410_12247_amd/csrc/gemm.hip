@@ -183,108 +183,114 @@ __device__ __forceinline__ void store_down(const floatx4 &v, int t, int m, int w
     if (row < m_valid && col < n_valid) *reinterpret_cast<floatx4 *>(out + row * ldo + col) = v;
 }
 
-    // K split: the piece stores its accumulators (each wave its own block,
-    // one 1 KiB store per fragment, through a buffer resource so the
-    // fragment offsets are scalars); split_fixup_kernel adds the pieces and
-    // runs the epilogue
-    template <class C>
+// K split: the piece stores its accumulators (each wave its own block,
+// one 1 KiB store per fragment, through a buffer resource so the
+// fragment offsets are scalars); split_fixup_kernel adds the pieces and
+// runs the epilogue
+template <class C>
 __device__ __forceinline__ void tile_store_piece(const floatx4 (&acc)[C::TN][C::TM], int wave,
                                                  const TileArgs &a) {
     const int wm = wave >> 1, lane = threadIdx.x & 63;
-        const __amdgpu_buffer_rsrc_t pres =
-            __builtin_amdgcn_make_buffer_rsrc(a.part, 0, -1, kBufferFlags);
-        const int loff = lane * 16;
-        // fragment rows wholly past the valid edge are never stored, so
-        // their partial sums are neither written nor read back (decode-sized
-        // tiles hold one or two valid rows of 320)
+    const __amdgpu_buffer_rsrc_t pres =
+        __builtin_amdgcn_make_buffer_rsrc(a.part, 0, -1, kBufferFlags);
+    const int loff = lane * 16;
+    // fragment rows wholly past the valid edge are never stored, so
+    // their partial sums are neither written nor read back (decode-sized
+    // tiles hold one or two valid rows of 320)
 #pragma unroll
-        for (int m = 0; m < C::TM; ++m) {
-            if (wm * C::WTM + m * 16 >= a.m_valid) break;
+    for (int m = 0; m < C::TM; ++m) {
+        if (wm * C::WTM + m * 16 >= a.m_valid) break;
 #pragma unroll
-            for (int t = 0; t < C::TN; ++t)
-                __builtin_amdgcn_raw_buffer_store_b128(
-                    __builtin_bit_cast(u32x4, acc[t][m]), pres, loff,
-                    wave * C::WAVE_BYTES + (t * C::TM + m) * 1024, 0);
-        }
+        for (int t = 0; t < C::TN; ++t)
+            __builtin_amdgcn_raw_buffer_store_b128(
+                __builtin_bit_cast(u32x4, acc[t][m]), pres, loff,
+                wave * C::WAVE_BYTES + (t * C::TM + m) * 1024, 0);
     }
+}
 
-    // Outputs of a whole tile.  A fragment leaves the MFMA with four columns of
+// Outputs of a whole tile.  A fragment leaves the MFMA with four columns of
 // 16 rows per lane; stored as it is, a request would scatter 16-byte (down)
 // or 8-byte (gate/up) pieces over 16 rows, each its own trip to the L2.  So
 // 16 x 64 blocks go through the wave's LDS scratch and leave as whole row
-// segments (256 or 128 bytes).  Every store is issued, whatever rows are
-// valid: lanes without a valid row get an offset past the resource's range,
-// which drops them.  With the next tile's first stages requested before
-// (PPTile), down GEMM us, scattered stores after the K loop -> this: DBRX
-// 8192 tokens 632 -> 576, Mixtral 16384 tokens 864 -> 831; dense FFN of 3001
-// rows x 5120 x 3072 237 -> 226; non-temporal stores: within 1%.
+// segments (256 or 128 bytes).  With another tile's stages requested before
+// (more), every store is issued, whatever rows are valid, since the waits
+// count them: lanes without a valid row get an offset past the resource's
+// range, which drops them; the workgroup's last tile leaves its empty blocks
+// out (dense FFN of 1 row x 4096 x 2048: 53.8 -> 52.2 us).  Down GEMM us,
+// scattered stores after the K loop -> this, with the next tile's first
+// stages requested before (PPTile): DBRX 8192 tokens 632 -> 576, Mixtral
+// 16384 tokens 864 -> 831; dense FFN of 3001 rows x 5120 x 3072 229 -> 217;
+// non-temporal stores: within 1%.
 template <int MODE, class C>
 __device__ __forceinline__ void tile_epilogue(const floatx4 (&acc)[C::TN][C::TM], bf16_t *smem,
-                                              int wave, const TileArgs &a) {
+                                              int wave, const TileArgs &a, bool more) {
     const int wn = wave & 1, wm = wave >> 1;
-        // (an opaque lane index: addresses computed from it are not hoisted
-        // over the K loop, which has no register to spare for them)
-        int lane = threadIdx.x & 63;
-        asm volatile("" : "+v"(lane));
-        char *sc = reinterpret_cast<char *>(smem) + C::SCRATCH + wave * C::SCRATCH_WAVE;
-        constexpr uint32_t RANGE = 0xFFFFFFF0u, DROP = 0xFFFFFFF8u;
-        const __amdgpu_buffer_rsrc_t ores =
-            __builtin_amdgcn_make_buffer_rsrc(a.out, 0, (int)RANGE, kBufferFlags);
-        const int row_w = (lane & 15) * C::SCRATCH_ROW;  // write: row lane % 16
-        if (MODE == 0) {
-            const int rr = lane >> 3, rc = lane & 7;  // read: 8 rows x 8 chunks of 16 bytes
-            const uint32_t colb = (uint32_t)(wn * 64 + rc * 8) * 2u;
-            const bool cols = wn * 64 < a.n_valid;
+    // (an opaque lane index: addresses computed from it are not hoisted
+    // over the K loop, which has no register to spare for them)
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));
+    char *sc = reinterpret_cast<char *>(smem) + C::SCRATCH + wave * C::SCRATCH_WAVE;
+    constexpr uint32_t RANGE = 0xFFFFFFF0u, DROP = 0xFFFFFFF8u;
+    const __amdgpu_buffer_rsrc_t ores =
+        __builtin_amdgcn_make_buffer_rsrc(a.out, 0, (int)RANGE, kBufferFlags);
+    const int row_w = (lane & 15) * C::SCRATCH_ROW;  // write: row lane % 16
+    if (MODE == 0) {
+        const int rr = lane >> 3, rc = lane & 7;  // read: 8 rows x 8 chunks of 16 bytes
+        const uint32_t colb = (uint32_t)(wn * 64 + rc * 8) * 2u;
+        const bool cols = wn * 64 < a.n_valid;
 #pragma unroll
-            for (int m = 0; m < C::TM; ++m) {
+        for (int m = 0; m < C::TM; ++m) {
+            if (!more && wm * C::WTM + m * 16 >= a.m_valid) break;
 #pragma unroll
-                for (int p = 0; p < 4; ++p) {
-                    const floatx4 g = acc[p][m], u = acc[p + 4][m];
-                    uint2 v;
-                    v.x = pack_bf16x2(silu_mul(g[0], u[0]), silu_mul(g[1], u[1]));
-                    v.y = pack_bf16x2(silu_mul(g[2], u[2]), silu_mul(g[3], u[3]));
-                    *reinterpret_cast<uint2 *>(sc + row_w + p * 32 + (lane >> 4) * 8) = v;
-                }
+            for (int p = 0; p < 4; ++p) {
+                const floatx4 g = acc[p][m], u = acc[p + 4][m];
+                uint2 v;
+                v.x = pack_bf16x2(silu_mul(g[0], u[0]), silu_mul(g[1], u[1]));
+                v.y = pack_bf16x2(silu_mul(g[2], u[2]), silu_mul(g[3], u[3]));
+                *reinterpret_cast<uint2 *>(sc + row_w + p * 32 + (lane >> 4) * 8) = v;
+            }
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const u32x4 v = *reinterpret_cast<const u32x4 *>(
+                    sc + (i * 8 + rr) * C::SCRATCH_ROW + rc * 16);
+                const int row = wm * C::WTM + m * 16 + i * 8 + rr;
+                const uint32_t off = cols && row < a.m_valid
+                                         ? (uint32_t)(row * a.ldo) * 2u + colb
+                                         : DROP;
+                __builtin_amdgcn_raw_buffer_store_b128(v, ores, off, 0, 0);
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+    } else {
+        const int rr = lane >> 4, rc = lane & 15;  // read: 4 rows x 16 chunks
+#pragma unroll
+        for (int m = 0; m < C::TM; ++m) {
+            if (!more && wm * C::WTM + m * 16 >= a.m_valid) break;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const bool cols = wn * 128 + h * 64 < a.n_valid;
+                const uint32_t colb = (uint32_t)(wn * 128 + h * 64 + rc * 4) * 4u;
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    *reinterpret_cast<floatx4 *>(sc + row_w + t * 64 + (lane >> 4) * 16) =
+                        acc[h * 4 + t][m];
                 __builtin_amdgcn_wave_barrier();
 #pragma unroll
-                for (int i = 0; i < 2; ++i) {
+                for (int i = 0; i < 4; ++i) {
                     const u32x4 v = *reinterpret_cast<const u32x4 *>(
-                        sc + (i * 8 + rr) * C::SCRATCH_ROW + rc * 16);
-                    const int row = wm * C::WTM + m * 16 + i * 8 + rr;
+                        sc + (i * 4 + rr) * C::SCRATCH_ROW + rc * 16);
+                    const int row = wm * C::WTM + m * 16 + i * 4 + rr;
                     const uint32_t off = cols && row < a.m_valid
-                                             ? (uint32_t)(row * a.ldo) * 2u + colb
+                                             ? (uint32_t)(row * a.ldo) * 4u + colb
                                              : DROP;
                     __builtin_amdgcn_raw_buffer_store_b128(v, ores, off, 0, 0);
                 }
                 __builtin_amdgcn_wave_barrier();
             }
-        } else {
-            const int rr = lane >> 4, rc = lane & 15;  // read: 4 rows x 16 chunks
-#pragma unroll
-            for (int m = 0; m < C::TM; ++m)
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const bool cols = wn * 128 + h * 64 < a.n_valid;
-                    const uint32_t colb = (uint32_t)(wn * 128 + h * 64 + rc * 4) * 4u;
-#pragma unroll
-                    for (int t = 0; t < 4; ++t)
-                        *reinterpret_cast<floatx4 *>(sc + row_w + t * 64 + (lane >> 4) * 16) =
-                            acc[h * 4 + t][m];
-                    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const u32x4 v = *reinterpret_cast<const u32x4 *>(
-                            sc + (i * 4 + rr) * C::SCRATCH_ROW + rc * 16);
-                        const int row = wm * C::WTM + m * 16 + i * 4 + rr;
-                        const uint32_t off = cols && row < a.m_valid
-                                                 ? (uint32_t)(row * a.ldo) * 4u + colb
-                                                 : DROP;
-                        __builtin_amdgcn_raw_buffer_store_b128(v, ores, off, 0, 0);
-                    }
-                    __builtin_amdgcn_wave_barrier();
-                }
         }
     }
+}
 
 // A workgroup's walk over its tiles: bind (operand addresses of a tile),
 // prologue (its first NS - 1 stages requested), kloop, epilogue.  The next
@@ -292,7 +298,17 @@ __device__ __forceinline__ void tile_epilogue(const floatx4 (&acc)[C::TN][C::TM]
 // so its first stages land while the outputs are written, and the waits of
 // its first stages leave the stores, which are younger, in flight (loads and
 // stores share one in-order vmcnt).
-template <int MODE, int BM_>
+//
+// SINGLE: the tile is the workgroup's only one, so nothing is sent behind its
+// last stages: the loop then requests a whole share in every stage (the last
+// stage again past the end) and waits for the same count, without a tail.  In
+// launches of few rows, bound by how fast requests go out, its fragment
+// reads also go before the requests; with many tiles per workgroup the
+// requests go first.  Dense FFN us, one workgroup per tile, loop with tail
+// and requests first -> this: 4096 x 2048, 1 row 55.3 -> 53.8; 3008 x 3008,
+// 200 rows 73.8 -> 68.7; 6144 x 1024, 700 rows 91.2 -> 86.3; 320-row tiles
+// the other way round: 5120 x 3072, 3001 rows 228 against 232.
+template <int MODE, int BM_, bool SINGLE>
 struct PPTile {
     using C = PPCfg<MODE, BM_>;
     static constexpr int BK = C::BK, NS = C::NS;
@@ -362,7 +378,7 @@ struct PPTile {
     template <class NX>
     __device__ __forceinline__ void issue(int ks, NX) {
         const uint32_t sb = lds0 + (uint32_t)((ks % NS) * C::STAGE * 2);
-        const uint32_t kb = (uint32_t)((k0 + ks) * BK * 2);
+        const uint32_t kb = (uint32_t)((k0 + (SINGLE ? min(ks, nk - 1) : ks)) * BK * 2);
 #pragma unroll
         for (int i = 0; i < C::W_INSTR; ++i)
             buf16_to_lds(wres, woff[i], kb, sb + (wave * (C::BN / 8) + i * C::RPI) * BK * 2);
@@ -379,7 +395,7 @@ struct PPTile {
 #pragma unroll
         for (int s = 0; s < NS - 1; ++s) {
             // (the copy of stage nk-1 goes to a buffer nothing reads)
-            const int back = max(s - (nk - 1), 0);
+            const int back = SINGLE ? 0 : max(s - (nk - 1), 0);
             k0 -= back;
             if (grp == 0) issue(s, nxa{}); else issue(s, nxb{});
             k0 += back;
@@ -417,6 +433,10 @@ struct PPTile {
             if (active) loop_a(stored, on{}); else loop_a(stored, off{});
         } else {
             if (active) loop_b(stored, on{}); else loop_b(stored, off{});
+        }
+        if (SINGLE) {  // the repeated requests
+            wait_vmcnt<0>();
+            __builtin_amdgcn_s_barrier();
         }
     }
 
@@ -458,19 +478,40 @@ struct PPTile {
                                                                         acc[t][m], 0, 0, 0);
     }
 
+    // Both loops: the stages that send a request run without a branch, the
+    // last ones in a loop of their own (branches around request and wait in
+    // one loop: 85 ns per 64-K stage, 128-row tiles).
     template <class W>
     __device__ __forceinline__ void loop_a(bool stored, W) {
         Frags f;
         load_frags(f, 0);
-        for (int k = 0; k < nk; ++k) {
-            // compute phase: stage k
+        auto compute = [&] {
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             __builtin_amdgcn_s_setprio(1);
             if constexpr (W::value) mfmas(f);
             __builtin_amdgcn_s_setprio(0);
-            // stage k+1 landed before the barrier; this wave's requests for
-            // stages k+2 .. k+NS-2 (and, older than those from the loop
-            // itself, the previous tile's stores) may stay in flight
+        };
+        // compute phase: stage k; then stage k+1 landed before the barrier:
+        // this wave's requests for stages k+2 .. k+NS-2 (and, older than
+        // those from the loop itself, the previous tile's stores) may stay in
+        // flight.  Memory phase: this wave's share of stage k+NS-1, fragments
+        // of stage k+1 (stale but in bounds past the end).
+        int k = 0;
+        for (; SINGLE ? k < nk : k + NS - 1 < nk; ++k) {
+            compute();
+            if (!SINGLE && stored && k <= NS - 3)
+                wait_vmcnt<(NS - 3) * C::LPS_A + C::STORES>();
+            else
+                wait_vmcnt<(NS - 3) * C::LPS_A>();
+            __builtin_amdgcn_s_barrier();
+            if (!SINGLE) issue(k + NS - 1, nxa{});
+            load_frags(f, k + 1);
+            if (SINGLE) issue(k + NS - 1, nxa{});
+            __builtin_amdgcn_s_barrier();
+        }
+        if (SINGLE) return;
+        for (; k < nk; ++k) {
+            compute();
             if (stored && k <= NS - 3 && k + NS - 1 <= nk)
                 wait_vmcnt<(NS - 3) * C::LPS_A + C::STORES>();
             else if (k + NS - 1 <= nk)
@@ -478,9 +519,6 @@ struct PPTile {
             else
                 wait_vmcnt<0>();
             __builtin_amdgcn_s_barrier();
-            // memory phase: this wave's share of stage k+NS-1, fragments of
-            // stage k+1 (stale but in bounds past the end)
-            if (k + NS - 1 < nk) issue(k + NS - 1, nxa{});
             load_frags(f, k + 1);
             __builtin_amdgcn_s_barrier();
         }
@@ -488,35 +526,45 @@ struct PPTile {
     template <class W>
     __device__ __forceinline__ void loop_b(bool stored, W) {
         Frags f;
-        for (int k = 0; k < nk; ++k) {
-            // memory phase: this wave's share of stage k+NS-1, fragments of stage k
-            if (k + NS - 1 < nk) issue(k + NS - 1, nxb{});
-            load_frags(f, k);
-            // stage k+1 landed; this wave's requests for stages k+2 ..
-            // k+NS-1 (the last just issued) may stay in flight
-            if (stored && k <= NS - 3 && k + NS <= nk)
-                wait_vmcnt<(NS - 2) * C::LPS_B + C::STORES>();
-            else if (k + NS <= nk)
-                wait_vmcnt<(NS - 2) * C::LPS_B>();
-            else if (NS > 3 && k + NS == nk + 1 && k > NS - 3)
-                wait_vmcnt<(NS - 3) * C::LPS_B>();
-            else
-                wait_vmcnt<0>();
+        auto compute = [&] {
             __builtin_amdgcn_s_barrier();
-            // compute phase: stage k
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             __builtin_amdgcn_s_setprio(1);
             if constexpr (W::value) mfmas(f);
             __builtin_amdgcn_s_setprio(0);
             __builtin_amdgcn_s_barrier();
+        };
+        // memory phase: this wave's share of stage k+NS-1, fragments of stage
+        // k; then stage k+1 landed: this wave's requests for stages k+2 ..
+        // k+NS-1 (the last just issued) may stay in flight.  Compute phase:
+        // stage k.
+        int k = 0;
+        for (; SINGLE ? k < nk : k + NS <= nk; ++k) {
+            if (!SINGLE) issue(k + NS - 1, nxb{});
+            load_frags(f, k);
+            if (SINGLE) issue(k + NS - 1, nxb{});
+            if (!SINGLE && stored && k <= NS - 3)
+                wait_vmcnt<(NS - 2) * C::LPS_B + C::STORES>();
+            else
+                wait_vmcnt<(NS - 2) * C::LPS_B>();
+            compute();
+        }
+        if (SINGLE) return;
+        for (; k < nk; ++k) {
+            load_frags(f, k);
+            if (NS > 3 && k + NS == nk + 1 && k > NS - 3)
+                wait_vmcnt<(NS - 3) * C::LPS_B>();
+            else
+                wait_vmcnt<0>();
+            compute();
         }
     }
 
     __device__ __forceinline__ void store_piece(const TileArgs &a) {
         tile_store_piece<C>(acc, wave, a);
     }
-    __device__ __forceinline__ void epilogue(const TileArgs &a) {
-        tile_epilogue<MODE, C>(acc, smem, wave, a);
+    __device__ __forceinline__ void epilogue(const TileArgs &a, bool more) {
+        tile_epilogue<MODE, C>(acc, smem, wave, a, more);
     }
 };
 
@@ -535,7 +583,7 @@ __device__ __forceinline__ void decode_tile(int tau, int MT, int NT, int &mt, in
 template <int MODE, int BM_>
 struct PingPong {
     using C = PPCfg<MODE, BM_>;  // also read by split_fixup_kernel
-    using Tile = PPTile<MODE, BM_>;
+    template <bool SINGLE> using Tile = PPTile<MODE, BM_, SINGLE>;
     static constexpr int THREADS = 64 * C::WAVES;
     static constexpr int BM = C::BM;
     static constexpr int BNOUT = C::BNOUT;
@@ -576,11 +624,12 @@ __global__ __launch_bounds__(TP::THREADS) void dense_kernel(const bf16_t *__rest
         a.out = reinterpret_cast<bf16_t *>(out) + m0 * ldo + n0;
     else
         a.out = reinterpret_cast<float *>(out) + m0 * ldo + n0;
-    typename TP::Tile tile(smem);
+    using Tile = typename TP::template Tile<TP::BM == 128>;
+    Tile tile(smem);
     tile.bind(a);
     tile.prologue();
-    tile.kloop(TP::Tile::NOTHING);
-    tile.epilogue(a);
+    tile.kloop(Tile::NOTHING);
+    tile.epilogue(a, false);
 }
 
 template <int MODE, class TP>
@@ -753,7 +802,7 @@ __global__ __launch_bounds__(TP::THREADS) void group_kernel(
         u += G;
         return true;
     };
-    using Tile = typename TP::Tile;
+    using Tile = typename TP::template Tile<false>;
     Tile tile(smem);
     TileArgs a;
     if (!take(a)) return;
@@ -772,7 +821,7 @@ __global__ __launch_bounds__(TP::THREADS) void group_kernel(
             tile.store_piece(a);
             after = Tile::PIECE;
         } else {
-            tile.epilogue(a);
+            tile.epilogue(a, more);
             after = Tile::STORES;
         }
         if (!more) break;
