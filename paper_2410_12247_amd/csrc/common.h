@@ -119,20 +119,40 @@ constexpr size_t kNoAllocScratchBytes = size_t(256) << 20;
 // logits: [T][E] fp32 scratch (may be NULL) for the many-expert, few-token
 // path (E > 16, T <= kRouteLogitsMaxTokens).
 constexpr int64_t kRouteLogitsMaxTokens = 4096;
+// Tokens of a workgroup of that path's selection launch.
+constexpr int kRouteSelectTokens = 4;
 // Up to this many tokens of at most 16 experts the router runs one chain per
 // lane (the chains' latency bounds it); beyond, the matrix-core kernel.
 constexpr int64_t kRouteChainMaxTokens = 512;
 // Widest row whose 256 rows of fp32 the router's 32-bit DMA offsets reach.
 constexpr int32_t kRouteDmaMaxHidden = 1 << 20;
+// Where the dispatch indices go (see launch_permute); NB buckets.
+struct DispatchOut {
+    int32_t *counts, *offsets, *counts_el, *sorted_slot, *slot_row;
+    int64_t tokens_per_stage;
+    int e0, EL, NB;
+};
+// disp (may be NULL): the dispatch indices to compute in the router's last
+// launch where route_dispatches says so.
 hipError_t launch_route(const moe_dims &d, const bf16_t *x, const float *wr, const float *bias,
-                        int32_t *ids, float *w, float *logits, hipStream_t s);
+                        int32_t *ids, float *w, float *logits, hipStream_t s,
+                        const DispatchOut *disp = nullptr);
+// Whether launch_route with these arguments can compute the dispatch indices:
+// its last launch is one workgroup.
+bool route_dispatches(const moe_dims &d, const bf16_t *x, const float *wr, const float *logits);
 // Its matrix-core form; x and wr 16-byte aligned.
 hipError_t launch_mfma_router(const moe_dims &d, const bf16_t *x, const float *wr,
                               const float *bias, int32_t *ids, float *w, float *logits,
-                              hipStream_t s);
+                              hipStream_t s, const DispatchOut *disp);
+// Whether launch_mfma_router sends the logits through their buffer to a
+// selection launch (four tokens per workgroup).
+bool mfma_router_selects_apart(const moe_dims &d, const float *logits);
 // Dispatch indices.  tokens_per_stage == 0: buckets are the local experts;
 // else bucket = (t / tokens_per_stage) * EL + local expert and counts_el
 // (may be NULL) receives the rows per local expert summed over stages.
+DispatchOut dispatch_out(const moe_dims &d, const WsLayout &L, int64_t tokens_per_stage,
+                         int32_t *counts, int32_t *offsets, int32_t *counts_el,
+                         int32_t *sorted_slot, int32_t *slot_row);
 hipError_t launch_permute(const moe_dims &d, const int32_t *ids, void *ws, const WsLayout &L,
                           int64_t tokens_per_stage, int32_t *counts, int32_t *offsets,
                           int32_t *counts_el, int32_t *sorted_slot, int32_t *slot_row,

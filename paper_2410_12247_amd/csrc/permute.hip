@@ -17,7 +17,7 @@
 //      slot_rank -> sorted_slot[row], slot_row[slot].
 // The gather copies whole rows with 16-byte loads and stores, one wave per
 // row.
-#include "common.h"
+#include "dispatch.h"
 
 namespace moe {
 namespace {
@@ -76,22 +76,6 @@ __global__ __launch_bounds__(64) void hist_kernel(const int32_t *__restrict__ id
         __syncthreads();
     }
     for (int e = lane; e < NB; e += 64) chunk_counts[(int64_t)blockIdx.x * NB + e] = cnt[e];
-}
-
-// Inclusive scan over a wave: DPP row_shr 1, 2, 4, 8 inside each 16-lane row
-// (lanes with no source add 0), then row totals carried with readlane.
-__device__ __forceinline__ int wave_inclusive_scan(int v) {
-    const int lane = threadIdx.x & 63;
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);  // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);  // row_shr:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);  // row_shr:8
-    const int r0 = __builtin_amdgcn_readlane(v, 15);
-    const int r1 = __builtin_amdgcn_readlane(v, 31);
-    const int r2 = __builtin_amdgcn_readlane(v, 47);
-    const int row = lane >> 4;
-    v += (row > 0 ? r0 : 0) + (row > 1 ? r1 : 0) + (row > 2 ? r2 : 0);
-    return v;
 }
 
 __global__ __launch_bounds__(256) void scan_kernel(const int32_t *__restrict__ chunk_counts,
@@ -168,84 +152,12 @@ __global__ __launch_bounds__(256) void scatter_kernel(const int32_t *__restrict_
 // hist_kernel, kept in registers; the bucket scan as in scan_kernel, 64
 // buckets at a time with a carry; then the rows.  Same counts, offsets and
 // rows as the three kernels.
-__global__ __launch_bounds__(64) void dispatch_one_chunk_kernel(
-    const int32_t *__restrict__ ids, int64_t nslots, int k, int e0, int EL, int64_t tps, int NB,
-    int32_t *__restrict__ counts, int32_t *__restrict__ offsets,
-    int32_t *__restrict__ counts_el, int32_t *__restrict__ sorted_slot,
-    int32_t *__restrict__ slot_row) {
+__global__ __launch_bounds__(64) void dispatch_one_chunk_kernel(const int32_t *__restrict__ ids,
+                                                                int64_t nslots, int k,
+                                                                DispatchOut o) {
     __shared__ int cnt[kMaxExperts];
     __shared__ int off[kMaxExperts];
-    const int lane = threadIdx.x;
-    for (int e = lane; e < NB; e += 64) cnt[e] = 0;
-    __syncthreads();
-    const uint64_t lt_mask = (1ull << lane) - 1ull;
-    constexpr int NIT = kPermChunk / 64;
-    // groups of 64 slots that hold any (the rest of the unrolled loops is
-    // skipped: decode batches have one or two)
-    const int nit = (int)((nslots + 63) / 64);
-    int idv[NIT], bucket[NIT], rank[NIT];
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) idv[it] = ids[min<int64_t>(it * 64 + lane, nslots - 1)];
-    asm volatile("" ::: "memory");
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-        bucket[it] = -1;
-        rank[it] = 0;
-        if (it >= nit) continue;
-        const int s = it * 64 + lane;
-        int e = idv[it] - e0;
-        if (s >= nslots || e < 0 || e >= EL) e = -1;
-        else if (tps > 0) e += (int)((uint32_t)s / (uint32_t)k / (uint32_t)tps) * EL;
-        const uint32_t v = (uint32_t)(e + 1);
-        uint64_t match = ~0ull;
-#pragma unroll
-        for (int b = 0; b < 9; ++b) {
-            const bool bit = (v >> b) & 1u;
-            const uint64_t bal = __ballot(bit);
-            match &= bit ? bal : ~bal;
-        }
-        const int before = __popcll(match & lt_mask);
-        bucket[it] = e;
-        rank[it] = e >= 0 ? cnt[e] + before : 0;
-        __syncthreads();
-        if (e >= 0 && before == 0) cnt[e] += __popcll(match);
-        __syncthreads();
-    }
-    int carry = 0;
-    for (int b0 = 0; b0 < NB; b0 += 64) {
-        const int e = b0 + lane;
-        const int v = e < NB ? cnt[e] : 0;
-        const int incl = wave_inclusive_scan(v);
-        if (e < NB) {
-            counts[e] = v;
-            off[e] = carry + incl - v;
-            offsets[e] = carry + incl - v;
-        }
-        carry += __builtin_amdgcn_readlane(incl, 63);
-    }
-    if (lane == 0) offsets[NB] = carry;
-    if (counts_el) {  // rows per local expert over the stages
-        for (int e = lane; e < EL; e += 64) {
-            int sum = 0;
-            for (int b = e; b < NB; b += EL) sum += cnt[b];
-            counts_el[e] = sum;
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-        const int s = it * 64 + lane;
-        if (it < nit && s < nslots) {
-            const int e = bucket[it];
-            if (e < 0) {
-                slot_row[s] = -1;
-            } else {
-                const int row = off[e] + rank[it];
-                sorted_slot[row] = s;
-                slot_row[s] = row;
-            }
-        }
-    }
+    dispatch_wave<kPermChunk / 64>(ids, nslots, k, o, cnt, off);
 }
 
 // One wave per row; rows [offsets[e_first], offsets[e_first+e_count]).
@@ -270,6 +182,14 @@ __global__ __launch_bounds__(256) void gather_kernel(const int32_t *__restrict__
 
 }  // namespace
 
+DispatchOut dispatch_out(const moe_dims &d, const WsLayout &L, int64_t tokens_per_stage,
+                         int32_t *counts, int32_t *offsets, int32_t *counts_el,
+                         int32_t *sorted_slot, int32_t *slot_row) {
+    return {counts,      offsets, tokens_per_stage > 0 ? counts_el : nullptr,
+            sorted_slot, slot_row, tokens_per_stage,
+            d.local_begin, d.local_count, L.nbuckets};
+}
+
 hipError_t launch_permute(const moe_dims &d, const int32_t *ids, void *ws, const WsLayout &L,
                           int64_t tokens_per_stage, int32_t *counts, int32_t *offsets,
                           int32_t *counts_el, int32_t *sorted_slot, int32_t *slot_row,
@@ -282,10 +202,9 @@ hipError_t launch_permute(const moe_dims &d, const int32_t *ids, void *ws, const
     const int64_t tps = tokens_per_stage;
     const int NB = L.nbuckets;
     if (nslots <= kPermChunk) {
-        dispatch_one_chunk_kernel<<<1, 64, 0, s>>>(ids, nslots, d.top_k, d.local_begin,
-                                                    d.local_count, tps, NB, counts, offsets,
-                                                    tps > 0 ? counts_el : nullptr, sorted_slot,
-                                                    slot_row);
+        dispatch_one_chunk_kernel<<<1, 64, 0, s>>>(
+            ids, nslots, d.top_k,
+            dispatch_out(d, L, tps, counts, offsets, counts_el, sorted_slot, slot_row));
         return hipGetLastError();
     }
     hist_kernel<<<(unsigned)L.nchunks, 64, 0, s>>>(ids, nslots, d.top_k, d.local_begin,

@@ -10,6 +10,7 @@
 
 #include <type_traits>
 
+#include "dispatch.h"
 #include "route_common.h"
 #include "route_lane_asm.h"
 
@@ -633,16 +634,17 @@ __device__ __forceinline__ float run_dpp(const floatx4 &xq, const HalfW &hv, flo
 // NQ: router-row DMA requests per block (4 rows of 256 bytes each); NS ring
 // slots, NS - 2 blocks of requests in flight; every expert is in the wave
 // (E <= 4 NQ) and it selects in place.  Dynamic LDS: NS * NQ KB of ring,
-// then the fp32 x row.
+// then the fp32 x row.  DISP (one token): the wave goes on to the dispatch
+// indices, a launch fewer.
 // (the body is a device function: the host pass of a kernel template whose
 // own body calls generic lambdas over target builtins emits no launch stub)
-template <int NQ, int NS>
+template <int NQ, int NS, bool DISP>
 __device__ __forceinline__ void route_chain(char *lds, const bf16_t *__restrict__ x,
                                             const float *__restrict__ wr,
                                             const float *__restrict__ bias, int64_t T, int H,
-                                            int E, int k, int renorm,
-                                            int32_t *__restrict__ ids,
-                                            float *__restrict__ wout) {
+                                            int E, int k, int renorm, int32_t *ids,
+                                            float *__restrict__ wout,
+                                            const DispatchOut &disp) {
     constexpr int SLOT = NQ * 1024;  // bytes: 4 NQ rows of 64 fp32
     constexpr int RING = NS * SLOT;
     static_assert(NS >= 3 && (NS - 2) * NQ <= 63 && RING <= 65536, "ring");
@@ -741,25 +743,37 @@ __device__ __forceinline__ void route_chain(char *lds, const bf16_t *__restrict_
     zs[lane] = z;
     __syncthreads();
     select_wave16(zs, t, E, k, renorm, lane, ids, wout);
+    if constexpr (DISP) {
+        __syncthreads();  // the ids are out, the logits read
+        int *cnt = reinterpret_cast<int *>(lds);
+        static_assert(NS * NQ * 1024 >= 8 * kMaxExperts, "counters fit the ring");
+        dispatch_wave<1>(ids, k, k, disp, cnt, cnt + kMaxExperts);
+    }
 }
 
-template <int NQ, int NS>
+template <int NQ, int NS, bool DISP>
 __global__ __launch_bounds__(64) void route_chain_kernel(const bf16_t *__restrict__ x,
                                                          const float *__restrict__ wr,
                                                          const float *__restrict__ bias,
                                                          int64_t T, int H, int E, int k,
-                                                         int renorm, int32_t *__restrict__ ids,
-                                                         float *__restrict__ wout) {
+                                                         int renorm, int32_t *ids,
+                                                         float *__restrict__ wout,
+                                                         DispatchOut disp) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    route_chain<NQ, NS>(lds, x, wr, bias, T, H, E, k, renorm, ids, wout);
+    route_chain<NQ, NS, DISP>(lds, x, wr, bias, T, H, E, k, renorm, ids, wout, disp);
 }
 
 template <int NQ, int NS>
 hipError_t launch_chain_q(const moe_dims &d, const bf16_t *x, const float *wr, const float *bias,
-                          int32_t *ids, float *w, hipStream_t s) {
+                          int32_t *ids, float *w, hipStream_t s, const DispatchOut *disp) {
     const size_t lds = (size_t)NS * NQ * 1024 + (size_t)d.hidden * 4;
-    route_chain_kernel<NQ, NS><<<(unsigned)d.tokens, 64, lds, s>>>(
-        x, wr, bias, d.tokens, d.hidden, d.experts, d.top_k, d.renormalize, ids, w);
+    if (disp)
+        route_chain_kernel<NQ, NS, true><<<1, 64, lds, s>>>(
+            x, wr, bias, d.tokens, d.hidden, d.experts, d.top_k, d.renormalize, ids, w, *disp);
+    else
+        route_chain_kernel<NQ, NS, false><<<(unsigned)d.tokens, 64, lds, s>>>(
+            x, wr, bias, d.tokens, d.hidden, d.experts, d.top_k, d.renormalize, ids, w,
+            DispatchOut{});
     return hipGetLastError();
 }
 
@@ -772,9 +786,10 @@ bool chain_fits(const moe_dims &d) {
                                   chain::kMaxLds;
 }
 hipError_t launch_chain(const moe_dims &d, const bf16_t *x, const float *wr, const float *bias,
-                        int32_t *ids, float *w, hipStream_t s) {
-    if (chain_requests(d) == 2) return launch_chain_q<2, kChainSlots>(d, x, wr, bias, ids, w, s);
-    return launch_chain_q<4, kChainSlots>(d, x, wr, bias, ids, w, s);
+                        int32_t *ids, float *w, hipStream_t s, const DispatchOut *disp) {
+    if (chain_requests(d) == 2)
+        return launch_chain_q<2, kChainSlots>(d, x, wr, bias, ids, w, s, disp);
+    return launch_chain_q<4, kChainSlots>(d, x, wr, bias, ids, w, s, disp);
 }
 
 // Per-SIMD fma work of a lane-router shape: every wave issues (G + 1) VALU
@@ -802,21 +817,36 @@ hipError_t launch_lane_router(const moe_dims &d, const bf16_t *x, const float *w
 
 }  // namespace
 
+namespace {
+// the LDS-DMA of the matrix-core and chain kernels copies 16-byte pieces at
+// 32-bit offsets from a workgroup's first row
+bool route_dma(const moe_dims &d, const bf16_t *x, const float *wr) {
+    return (((uintptr_t)x | (uintptr_t)wr) & 15) == 0 && d.hidden <= kRouteDmaMaxHidden;
+}
+// Up to 512 tokens of at most 16 experts: a chain per lane, whose dependent
+// fma is shorter than a quarter of the matrix core's (us, chain against
+// matrix core: Mixtral 64 tokens 16.2 / 21.6, 512 tokens 19.9 / 22.1; DBRX
+// 512 tokens 30.0 / 32.4).
+bool route_by_chain(const moe_dims &d) {
+    return d.tokens <= kRouteChainMaxTokens && chain_fits(d);
+}
+}  // namespace
+
+bool route_dispatches(const moe_dims &d, const bf16_t *x, const float *wr, const float *logits) {
+    if (d.tokens <= 0 || !route_dma(d, x, wr)) return false;
+    // a chain workgroup is one token, a selection workgroup four
+    if (route_by_chain(d)) return d.tokens == 1;
+    return d.tokens <= kRouteSelectTokens && mfma_router_selects_apart(d, logits);
+}
+
 hipError_t launch_route(const moe_dims &d, const bf16_t *x, const float *wr, const float *bias,
-                        int32_t *ids, float *w, float *logits, hipStream_t s) {
+                        int32_t *ids, float *w, float *logits, hipStream_t s,
+                        const DispatchOut *disp) {
     if (d.tokens <= 0) return hipSuccess;
-    // the LDS-DMA of the matrix-core and chain kernels copies 16-byte pieces
-    // at 32-bit offsets from a workgroup's first row
-    const bool aligned =
-        (((uintptr_t)x | (uintptr_t)wr) & 15) == 0 && d.hidden <= kRouteDmaMaxHidden;
-    if (aligned) {
-        // up to 512 tokens of at most 16 experts: a chain per lane, whose
-        // dependent fma is shorter than a quarter of the matrix core's (us,
-        // chain against matrix core: Mixtral 64 tokens 16.2 / 21.6, 512
-        // tokens 19.9 / 22.1; DBRX 512 tokens 30.0 / 32.4)
-        if (d.tokens <= kRouteChainMaxTokens && chain_fits(d))
-            return launch_chain(d, x, wr, bias, ids, w, s);
-        return launch_mfma_router(d, x, wr, bias, ids, w, logits, s);
+    if (disp && !route_dispatches(d, x, wr, logits)) return hipErrorInvalidValue;
+    if (route_dma(d, x, wr)) {
+        if (route_by_chain(d)) return launch_chain(d, x, wr, bias, ids, w, s, disp);
+        return launch_mfma_router(d, x, wr, bias, ids, w, logits, s, disp);
     }
     // any alignment: the lane-per-token kernel, or the register-tiled one
     // for more than 16 experts

@@ -32,22 +32,30 @@
 // L2 channels.
 #include <algorithm>
 
+#include "dispatch.h"
 #include "route_common.h"
 
 namespace moe {
 namespace {
 
-constexpr int kSelectThreads = 256;
+constexpr int kSelectThreads = 64 * kRouteSelectTokens;
 
-// Top-k of logits z [T][E] (any E): one wave per token.
+// Top-k of logits z [T][E] (any E): one wave per token.  DISP (one
+// workgroup): its first wave goes on to the dispatch indices.
+template <bool DISP>
 __global__ __launch_bounds__(kSelectThreads) void route_select_kernel(const float *__restrict__ z,
                                                                   int64_t T, int E, int k,
-                                                                  int renorm,
-                                                                  int32_t *__restrict__ ids,
-                                                                  float *__restrict__ wout) {
-    const int64_t t = (int64_t)blockIdx.x * (kSelectThreads / 64) + (threadIdx.x >> 6);
-    if (t >= T) return;
-    select_token(z + t * E, t, E, k, renorm, threadIdx.x & 63, ids, wout);
+                                                                  int renorm, int32_t *ids,
+                                                                  float *__restrict__ wout,
+                                                                  DispatchOut disp) {
+    const int64_t t = (int64_t)blockIdx.x * kRouteSelectTokens + (threadIdx.x >> 6);
+    if (t < T) select_token(z + t * E, t, E, k, renorm, threadIdx.x & 63, ids, wout);
+    if constexpr (DISP) {
+        __shared__ int cnt[kMaxExperts], off[kMaxExperts];
+        static_assert(kRouteSelectTokens * kMaxTopK <= 64, "one group of slots");
+        __syncthreads();  // every token's ids are out
+        if (threadIdx.x < 64) dispatch_wave<1>(ids, T * k, k, disp, cnt, off);
+    }
 }
 
 namespace mfma {
@@ -325,7 +333,8 @@ hipError_t launch_mfma(const moe_dims &d, const bf16_t *x, const float *wr, cons
 
 template <int TT, int TE, int TW, int EW, int NS>
 hipError_t launch_mfma_z(const moe_dims &d, const bf16_t *x, const float *wr, const float *bias,
-                         int32_t *ids, float *w, float *z, hipStream_t s) {
+                         int32_t *ids, float *w, float *z, hipStream_t s,
+                         const DispatchOut *disp) {
     using C = mfma::Cfg<TT, TE, TW, EW, NS>;
     const dim3 grid((unsigned)((d.tokens + C::TOK - 1) / C::TOK),
                     (unsigned)((d.experts + C::EP - 1) / C::EP));
@@ -333,8 +342,14 @@ hipError_t launch_mfma_z(const moe_dims &d, const bf16_t *x, const float *wr, co
         x, wr, bias, d.tokens, d.hidden, d.experts, d.top_k, d.renormalize, ids, w, z);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    route_select_kernel<<<(unsigned)((d.tokens + 3) / 4), kSelectThreads, 0, s>>>(
-        z, d.tokens, d.experts, d.top_k, d.renormalize, ids, w);
+    if (disp)
+        route_select_kernel<true><<<1, kSelectThreads, 0, s>>>(
+            z, d.tokens, d.experts, d.top_k, d.renormalize, ids, w, *disp);
+    else
+        route_select_kernel<false>
+            <<<(unsigned)((d.tokens + kRouteSelectTokens - 1) / kRouteSelectTokens),
+               kSelectThreads, 0, s>>>(z, d.tokens, d.experts, d.top_k, d.renormalize, ids, w,
+                                       DispatchOut{});
     return hipGetLastError();
 }
 
@@ -369,11 +384,30 @@ hipError_t launch_mfma_te(const moe_dims &d, const bf16_t *x, const float *wr, c
     if (c32 == best) return launch_mfma_ring<1, TE, 2, 2>(d, x, wr, bias, ids, w, s);
     return launch_mfma_ring<1, TE4, 1, 4>(d, x, wr, bias, ids, w, s);
 }
+// expert blocks, and per wave with the experts over two waves (1 .. 6 or 8)
+int expert_blocks(const moe_dims &d) { return (d.experts + 15) / 16; }
+int blocks_per_wave(int eb) { return eb > 12 ? 8 : (eb + 1) / 2; }
+// waves of one tile each
+int64_t tile_waves(const moe_dims &d) { return (d.tokens + 15) / 16 * expert_blocks(d); }
 }  // namespace
+
+// Few tokens: the expert blocks over workgroups of their own (logits through
+// the caller's buffer), one tile per wave; a round of a tile per SIMD takes
+// 20 us, the selection kernel is in the other 10 (E = 160, us, against the
+// experts in one workgroup: 61 tokens 28 against 68, 1027 tokens 31 against
+// 69, 2048 tokens 49 against 70).
+bool mfma_router_selects_apart(const moe_dims &d, const float *logits) {
+    if (d.experts <= 16 || !logits || d.tokens > kRouteLogitsMaxTokens) return false;
+    const int eb = expert_blocks(d);
+    const int64_t simds = 4 * (int64_t)device_cu_count();
+    const double cz = (double)((tile_waves(d) + simds - 1) / simds) * 20.0 + 10.0;
+    return cz <= std::min(mfma_cost(d.tokens, 16, (eb + 3) / 4),
+                          mfma_cost(d.tokens, 32, blocks_per_wave(eb)));
+}
 
 hipError_t launch_mfma_router(const moe_dims &d, const bf16_t *x, const float *wr,
                               const float *bias, int32_t *ids, float *w, float *logits,
-                              hipStream_t s) {
+                              hipStream_t s, const DispatchOut *disp) {
     if (d.experts <= 16) {
         // one 16 x 16 tile per wave; single-wave workgroups spread up to one
         // tile per compute unit and SIMD better, above that the smaller ring
@@ -383,23 +417,12 @@ hipError_t launch_mfma_router(const moe_dims &d, const bf16_t *x, const float *w
             return launch_mfma<1, 1, 1, 1, 8>(d, x, wr, bias, ids, w, s);
         return launch_mfma<1, 1, 4, 1, 4>(d, x, wr, bias, ids, w, s);
     }
-    const int eb = (d.experts + 15) / 16;  // expert blocks
-    const int te = eb > 12 ? 8 : (eb + 1) / 2;  // 1 .. 6 or 8
-    if (logits && d.tokens <= kRouteLogitsMaxTokens) {
-        // few tokens: the expert blocks over workgroups of their own (logits
-        // through the caller's buffer), one tile per wave; a round of a tile
-        // per SIMD takes 20 us, the selection kernel is in the other 10
-        // (E = 160, us, against the experts in one workgroup: 61 tokens 28
-        // against 68, 1027 tokens 31 against 69, 2048 tokens 49 against 70)
-        const int64_t waves = (d.tokens + 15) / 16 * eb, simds = 4 * (int64_t)device_cu_count();
-        const double cz = (double)((waves + simds - 1) / simds) * 20.0 + 10.0;
-        if (cz <= std::min(mfma_cost(d.tokens, 16, (eb + 3) / 4), mfma_cost(d.tokens, 32, te))) {
-            if (waves <= simds)
-                return launch_mfma_z<1, 1, 1, 1, 6>(d, x, wr, bias, ids, w, logits, s);
-            return launch_mfma_z<1, 1, 2, 2, 3>(d, x, wr, bias, ids, w, logits, s);
-        }
+    if (mfma_router_selects_apart(d, logits)) {
+        if (tile_waves(d) <= 4 * (int64_t)device_cu_count())
+            return launch_mfma_z<1, 1, 1, 1, 6>(d, x, wr, bias, ids, w, logits, s, disp);
+        return launch_mfma_z<1, 1, 2, 2, 3>(d, x, wr, bias, ids, w, logits, s, disp);
     }
-    switch (te) {
+    switch (blocks_per_wave(expert_blocks(d))) {
         case 1: return launch_mfma_te<1>(d, x, wr, bias, ids, w, s);
         case 2: return launch_mfma_te<2>(d, x, wr, bias, ids, w, s);
         case 3: return launch_mfma_te<3>(d, x, wr, bias, ids, w, s);

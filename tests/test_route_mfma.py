@@ -74,3 +74,33 @@ def test_unaligned_rows(E):
     x.copy_(bf16(xb))
     assert x.data_ptr() % 16 == 8
     check(x, f32(wr), f32(bias), ids, w, T, E, H, k, True)
+
+
+@pytest.mark.parametrize("E", [8, 16, 17, 160])
+@pytest.mark.parametrize("T", [1, 3, 4, 5])
+def test_dispatch_behind_the_router(T, E):
+    """A router launch of one workgroup also computes the dispatch indices;
+    with every phase timed they take a launch of their own.  The same bits,
+    whole and in expert or token stages, and the row counts of the ids."""
+    H, I, k = 128, 64, 8
+    xb, wr, bias = draw(T, E, H, True, 7 * T + E)
+    rng = np.random.default_rng(E)
+    w = lambda *s: bf16(synth.bf16_bits(  # noqa: E731
+        rng.standard_normal(s, dtype=np.float32) * np.float32(0.05)))
+    e0, EL = (1, 6) if E < 100 else (30, 100)
+    wg, wu, wd = w(EL, I, H), w(EL, I, H), w(EL, H, I)
+    d = moe.dims(T, H, I, E, k, e0, EL, True)
+    for stage in ({}, {"pipeline_n": 2}, {"pipeline_n": 2, "chunk_mode": moe.CHUNK_TOKENS}):
+        if stage.get("chunk_mode") is not None and (T < 2 or 2 * EL > 256):
+            continue
+        out = []
+        for timing in (False, True):
+            b = moe.MoEBuffers(d, moe.opts(timing=timing, exact_order=True, **stage))
+            b.run(bf16(xb), f32(wr), f32(bias), wg, wu, wd)
+            torch.cuda.synchronize()
+            out.append((b.y.cpu(), b.topk_ids.cpu(), b.topk_w.cpu(), b.counts.cpu()))
+        for a, c in zip(*out):
+            assert torch.equal(a, c)
+        ids = out[0][1].numpy().ravel() - e0
+        want = np.bincount(ids[(ids >= 0) & (ids < EL)], minlength=EL)
+        assert np.array_equal(out[0][3].numpy(), want)
