@@ -23,8 +23,9 @@ constexpr int RT_THREADS = 256;
 // alignment).
 //
 // Logits phase layout: 256 threads = TG token groups x EG expert groups
-// (EG = 16); a thread owns TT tokens (tg + TG i: consecutive lanes read rows 36 floats apart, so
-// eight lanes of a 16-byte LDS read land on distinct banks) x TE experts
+// (EG = 16); a thread owns TT tokens (tg + TG i: consecutive lanes read rows
+// 36 floats apart, so eight lanes of a 16-byte LDS read land on distinct
+// banks) x TE experts
 // (TE = ceil(E / EG)) and keeps their fma chains in registers.  x and the
 // router are staged through two LDS buffers HC h at a time: the router rows
 // by LDS-DMA, x through registers (widened to fp32), the next chunk in
