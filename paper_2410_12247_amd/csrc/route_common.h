@@ -93,13 +93,16 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
     return max(max(a, b), max(c, d));
 }
 
-// Top-k and softmax weights of N tokens t0, t0 + step, .. (those below T)
-// from their E logits (zrow[i]), by one wave: lane l holds experts l, l+64,
-// l+128, l+192; each of the k rounds takes the wave-wide max of the logits'
+// Top-k and softmax weights of the N tokens t[i] (those below T) from their
+// E logits zrow[i], by one wave: lane l holds experts l, l+64, l+128, l+192;
+// each of the k rounds takes the wave-wide max of the logits'
 // order-preserving bits and, among the lanes that hold it, the lowest expert
 // (a ballot per 64 experts); the weights are fp64 softmax values rounded
 // once to fp32, lane j taking the j-th selected expert's.  Several tokens
-// at once hide each other's cross-lane latency.
+// at once hide each other's cross-lane latency.  A token's k experts are
+// distinct whatever its logits (the row counts and buffers downstream rely
+// on it): bits of 0 mark a taken expert but are also those of the NaN of all
+// one bits, so once nothing above 0 is left the taken experts are compared.
 template <int N>
 __device__ __forceinline__ void select_tokens(const float *const (&zrow)[N],
                                               const int64_t (&t)[N], int64_t T, int E, int k,
@@ -130,6 +133,15 @@ __device__ __forceinline__ void select_tokens(const float *const (&zrow)[N],
             for (int q = 3; q >= 0; --q) {
                 const uint64_t m = __builtin_amdgcn_ballot_w64(ord[i][q] == best);
                 if (m) e = 64 * q + __builtin_ctzll(m);
+            }
+            if (best == 0u) {  // the lowest expert not taken
+                for (int q = 3; q >= 0; --q) {
+                    bool left = lane + 64 * q < E;
+                    for (int p = 0; p < j; ++p)
+                        left &= __builtin_amdgcn_readlane(my_e[i], p) != lane + 64 * q;
+                    const uint64_t m = __builtin_amdgcn_ballot_w64(left);
+                    if (m) e = 64 * q + __builtin_ctzll(m);
+                }
             }
 #pragma unroll
             for (int q = 0; q < 4; ++q)

@@ -63,6 +63,41 @@ def test_masked_experts(T, E):
     check(bf16(xb), f32(wr), f32(bias), ids, w, T, E, 128, 3, False)
 
 
+@pytest.mark.parametrize("T,E,k,call", [(5, 8, 8, "route"), (700, 8, 8, "route"),
+                                         (3, 20, 6, "route"), (600, 160, 8, "route"),
+                                         (70, 256, 8, "forward"), (2, 40, 8, "forward")])
+def test_nan_logits_pick_distinct_experts(T, E, k, call):
+    """NaN logits have no defined weights, but a token's experts stay distinct:
+    the finite ones first, then the NaNs of all one bits (the lowest key there
+    is) by index.  A repeated expert would exceed the row bounds that the
+    dispatch buffers and the GEMM tiles are sized by."""
+    H = 128
+    xb, wr, bias = draw(T, E, H, True, T + E)
+    finite = [1, E // 2, E - 1]
+    b = np.full(E, 0xFFFFFFFF, np.uint32)
+    b[finite] = bias[finite].view(np.uint32)
+    bias = b.view(np.float32)
+    d = moe.dims(T, H, 64, E, k, E - 3, 3, renormalize=False)
+    if call == "route":
+        ids = torch.full((T, k), -1, dtype=torch.int32, device=dev())
+        moe.route(d, bf16(xb), f32(wr), f32(bias), ids,
+                  torch.empty((T, k), dtype=torch.float32, device=dev()))
+        counts = None
+    else:
+        w = torch.zeros((3, 64, H), dtype=torch.bfloat16, device=dev())
+        buf = moe.MoEBuffers(d, moe.opts())
+        buf.run(bf16(xb), f32(wr), f32(bias), w, w, w.view(3, H, 64))
+        ids, counts = buf.topk_ids, buf.counts.cpu().numpy()
+    torch.cuda.synchronize()
+    ids = ids.cpu().numpy()
+    assert np.array_equal(np.sort(ids[:, :3], axis=1), np.tile(sorted(finite), (T, 1)))
+    rest = [e for e in range(E) if e not in finite][:k - 3]
+    assert np.array_equal(ids[:, 3:], np.tile(rest, (T, 1)))
+    if counts is not None:
+        assert counts.max() <= T and counts.tolist() == [
+            int((ids == e).sum()) for e in range(E - 3, E)]
+
+
 @pytest.mark.parametrize("E", [40, 160])
 def test_unaligned_rows(E):
     """x eight bytes off a 16-byte boundary."""
