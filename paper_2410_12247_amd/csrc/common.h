@@ -124,8 +124,6 @@ constexpr int kRouteSelectTokens = 4;
 // Up to this many tokens of at most 16 experts the router runs one chain per
 // lane (the chains' latency bounds it); beyond, the matrix-core kernel.
 constexpr int64_t kRouteChainMaxTokens = 512;
-// Widest row whose 256 rows of fp32 the router's 32-bit DMA offsets reach.
-constexpr int32_t kRouteDmaMaxHidden = 1 << 20;
 // Where the dispatch indices go (see launch_permute); NB buckets.
 struct DispatchOut {
     int32_t *counts, *offsets, *counts_el, *sorted_slot, *slot_row;
@@ -139,14 +137,18 @@ hipError_t launch_route(const moe_dims &d, const bf16_t *x, const float *wr, con
                         const DispatchOut *disp = nullptr);
 // Whether launch_route with these arguments can compute the dispatch indices:
 // its last launch is one workgroup.
-bool route_dispatches(const moe_dims &d, const bf16_t *x, const float *wr, const float *logits);
-// Its matrix-core form; x and wr 16-byte aligned.
+bool route_dispatches(const moe_dims &d, const bf16_t *x, const float *logits);
+// Its matrix-core form; x 16-byte aligned.
 hipError_t launch_mfma_router(const moe_dims &d, const bf16_t *x, const float *wr,
                               const float *bias, int32_t *ids, float *w, float *logits,
                               hipStream_t s, const DispatchOut *disp);
 // Whether launch_mfma_router sends the logits through their buffer to a
 // selection launch (four tokens per workgroup).
 bool mfma_router_selects_apart(const moe_dims &d, const float *logits);
+// That launch: top-k and weights of the logits z [T][E]; disp (at most
+// kRouteSelectTokens tokens) as in launch_route.
+hipError_t launch_route_select(const moe_dims &d, const float *z, int32_t *ids, float *w,
+                               hipStream_t s, const DispatchOut *disp);
 // Dispatch indices.  tokens_per_stage == 0: buckets are the local experts;
 // else bucket = (t / tokens_per_stage) * EL + local expert and counts_el
 // (may be NULL) receives the rows per local expert summed over stages.

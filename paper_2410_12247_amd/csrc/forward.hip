@@ -591,7 +591,7 @@ moe_status forward_impl(const moe_dims &d, const moe_opts &opt, const moe_bf16 *
     // each other's ids.
     float *logits = L.logits ? reinterpret_cast<float *>(base + L.logits) : nullptr;
     const bool fused = !(timing && (o->flags & MOE_FLAG_TIMING)) &&
-                       route_dispatches(d, x, w_router, logits);
+                       route_dispatches(d, x, logits);
     const DispatchOut disp =
         dispatch_out(d, L, tps, cnt, off, cnt_el, sorted_slot, slot_row);
     {

@@ -4,8 +4,8 @@
 // h in ascending order, started from +0, with the bias added once at the
 // end -- the same bits as a sequential fma loop on the CPU, from every
 // kernel: the matrix-core one (route_mfma.hip), the chain-per-lane one for a
-// few tokens of at most 16 experts, and, for operands that are not 16-byte
-// aligned, the lane-per-token and register-tiled ones.
+// few tokens of at most 16 experts, and, where x is not 16-byte aligned, the
+// lane-per-token and register-tiled ones.
 #include "common.h"
 
 #include <type_traits>
@@ -19,14 +19,13 @@ namespace {
 
 constexpr int RT_THREADS = 256;
 
-// Register-tiled router for more than 16 experts (operands of any
-// alignment).
+// Register-tiled router for more than 16 experts (x of any alignment).
 //
 // Logits phase layout: 256 threads = TG token groups x EG expert groups
-// (EG = 16); a thread owns TT tokens (tg + TG i: consecutive lanes read rows
-// 36 floats apart, so eight lanes of a 16-byte LDS read land on distinct
-// banks) x TE experts
-// (TE = ceil(E / EG)) and keeps their fma chains in registers.  x and the
+// (EG = 16, or 32 for 129 to 160 experts); a thread owns TT tokens (tg + TG
+// i: consecutive lanes read rows 36 floats apart, so eight lanes of a 16-byte
+// LDS read land on distinct banks) x TE experts (TE = ceil(E / EG)) and keeps
+// their fma chains in registers.  x and the
 // router are staged through two LDS buffers HC h at a time: the router rows
 // by LDS-DMA, x through registers (widened to fp32), the next chunk in
 // flight while the current one is multiplied; per 4 h a thread reads
@@ -35,7 +34,7 @@ constexpr int RT_THREADS = 256;
 // TT tokens per thread, so a workgroup routes TG*TT <= 64 tokens; the
 // launcher picks TT so that the grid keeps several workgroups per compute
 // unit.
-template <int TE, int TT, int RT_EG, int HC>
+template <int TE, int TT, int RT_EG>
 __global__ __launch_bounds__(RT_THREADS) void route_kernel(const bf16_t *__restrict__ x,
                                                            const float *__restrict__ wr,
                                                            const float *__restrict__ bias,
@@ -45,9 +44,8 @@ __global__ __launch_bounds__(RT_THREADS) void route_kernel(const bf16_t *__restr
     constexpr int RT_TG = RT_THREADS / RT_EG;  // token groups
     constexpr int RT_TOK = RT_TG * TT;          // tokens per workgroup
     static_assert(RT_TOK <= 64, "a workgroup routes at most 64 tokens");
-    static_assert(HC % 32 == 0, "router rows are staged in 128-byte segments");
     constexpr int RT_TT = TT;
-    constexpr int RT_HC = HC;
+    constexpr int HC = 32, RT_HC = HC;  // h per stage: router rows in 128-byte segments
     constexpr int RT_LD = HC + 4;       // x row stride in LDS (floats)
     constexpr int EMAX = RT_EG * TE;
     constexpr int XS = RT_TOK * RT_LD;  // floats of one x stage
@@ -181,9 +179,10 @@ __global__ __launch_bounds__(RT_THREADS) void route_kernel(const bf16_t *__restr
     }
 }
 
-// Lane-per-token router (E <= 16, operands of any alignment).  Lane l of a
-// wave owns the chains of token l % TPW for R * G experts (the wave's 64 lanes are R sets of TPW =
-// 64 / R tokens; set s takes G experts of its own): x is the lane's own
+// Lane-per-token router (E <= 16, and blocks of 16 experts for more experts
+// and few tokens; x of any alignment).  Lane l of a wave owns the chains of
+// token l % TPW for R * G experts (the wave's 64 lanes are R sets of TPW = 64
+// / R tokens; set s takes G experts of its own): x is the lane's own
 // operand, and the router element of each fma comes from a register that
 // holds 16 consecutive h in each 16-lane row, broadcast by DPP (see
 // route_lane_asm.h), so a stage of 64 h costs 64 G fmas plus 64 bf16
@@ -201,7 +200,13 @@ __global__ __launch_bounds__(RT_THREADS) void route_kernel(const bf16_t *__restr
 // themselves left it behind their VALU stream: measured on the Mixtral shape
 // (16384 tokens, H = 4096, 8 experts), 41 us that way against 36 us with the
 // producer wave.  The logits then go to LDS and one lane per token takes the
-// top-k and the softmax weights.
+// top-k and the softmax weights; in the expert-block form (ZOUT) they go to
+// a [T][E] buffer for the selection launch.  For more than 16 experts the
+// chain per lane is as long as for 16 (H fmas), so up to a few thousand
+// tokens this beats the register-tiled kernel, whose workgroups each run
+// 5 to 20 chains per thread (the forward, x off 16-byte alignment, register
+// tiles -> this: E = 160, H = 5120: 64 tokens 296 -> 69 us, 4096 tokens 352
+// -> 240; E = 40, H = 4096: 1 token 137 -> 59 us).
 constexpr int RL_HS = 64;     // h per stage
 constexpr int RL_NS_MAX = 6;  // ring stages at most (deeper rings measured no faster)
 
@@ -345,14 +350,18 @@ __device__ __forceinline__ void select_wave16(const float *zrow, int64_t t, int 
     }
 }
 
-template <int G, int R, int NW, int NS>
+// ZOUT: the workgroup takes experts blockIdx.y * EP .. (any E) and writes
+// its logits (bias added) to zout; else one workgroup holds every expert
+// (E <= EP) and selects in place.
+template <int G, int R, int NW, int NS, bool ZOUT>
 __global__ __launch_bounds__(64 * NW + 64) void route_lane_kernel(const bf16_t *__restrict__ x,
                                                              const float *__restrict__ wr,
                                                              const float *__restrict__ bias,
                                                              int64_t T, int H, int E, int k,
                                                              int renorm,
                                                              int32_t *__restrict__ ids,
-                                                             float *__restrict__ wout) {
+                                                             float *__restrict__ wout,
+                                                             float *__restrict__ zout) {
     constexpr int TPW = 64 / R;              // tokens per wave (and per workgroup)
     constexpr int EP = NW * R * G;           // experts per workgroup
     constexpr int XB = TPW * RL_HS * 2;      // bytes of a stage's x rows
@@ -377,6 +386,7 @@ __global__ __launch_bounds__(64 * NW + 64) void route_lane_kernel(const bf16_t *
     const int tl = lane % TPW;                   // token of this lane
     const int eb = (wave * R + lane / TPW) * G;  // its first expert in the block
     const int64_t t0 = (int64_t)blockIdx.x * TPW;
+    const int e0 = ZOUT ? (int)blockIdx.y * EP : 0;  // the block's first expert
 
     // the producer's DMA requests q of a stage: q < NXR: 8 x rows of 128
     // bytes (lane i: row 8 q + i / 8, 16-byte chunk (i % 8) ^ lane_swz(row)
@@ -395,7 +405,7 @@ __global__ __launch_bounds__(64 * NW + 64) void route_lane_kernel(const bf16_t *
             step_bytes[q] = RL_HS * 2;
         } else {
             const int qw = q - NXR;
-            const int e = min(qw * 4 + (lane >> 4), E - 1);  // rows past E: unused copies
+            const int e = min(e0 + qw * 4 + (lane >> 4), E - 1);  // rows past E: unused copies
             src[q] = reinterpret_cast<const char *>(wr + (int64_t)e * H) + (lane & 15) * 16;
             dst[q] = XB + qw * 1024;
             step_bytes[q] = RL_HS * 4;
@@ -457,6 +467,17 @@ __global__ __launch_bounds__(64 * NW + 64) void route_lane_kernel(const bf16_t *
         for (int st0 = 0; st0 < nst; st0 += NS)
             lane_unroll<0, NS>([&](auto u) { step(st0 + decltype(u)::value, u); });
     }
+    if constexpr (ZOUT) {
+        // (the producer's DMA has all been waited for: its last wait is vmcnt(0))
+        if (producer) return;
+        const int64_t t = t0 + tl;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const int e = e0 + eb + g;
+            if (e < E && t < T) zout[t * E + e] = bias ? acc[g] + bias[e] : acc[g];
+        }
+        return;
+    }
     __syncthreads();  // no wave reads the ring any more; no DMA in flight
 
     // logits to LDS, zs[token][e] with an odd row stride
@@ -479,21 +500,22 @@ hipError_t launch_tt(const moe_dims &d, const bf16_t *x, const float *wr, const 
                      int32_t *ids, float *w, hipStream_t s) {
     constexpr int TOK = RT_THREADS / EG * TT;
     const int64_t blocks = (d.tokens + TOK - 1) / TOK;
-    route_kernel<TE, TT, EG, 32><<<(unsigned)blocks, RT_THREADS, 0, s>>>(
+    route_kernel<TE, TT, EG><<<(unsigned)blocks, RT_THREADS, 0, s>>>(
         x, wr, bias, d.tokens, d.hidden, d.experts, d.top_k, d.renormalize, ids, w);
     return hipGetLastError();
 }
 
-template <int TE, int EG = 16>
+template <int TE>
 hipError_t launch_te(const moe_dims &d, const bf16_t *x, const float *wr, const float *bias,
                      int32_t *ids, float *w, hipStream_t s) {
     // the most tokens per thread (fewest LDS reads per fma) that still
     // leaves enough workgroups per CU to hide latency
-    constexpr int TG = RT_THREADS / EG;
+    constexpr int EG = 16, TG = RT_THREADS / EG;
     const int cus = device_cu_count();
-    if (TG * 4 <= 64 && d.tokens >= (int64_t)TG * 4 * 4 * cus)
-        return launch_tt<TE, (TG * 4 <= 64 ? 4 : 1), EG>(d, x, wr, bias, ids, w, s);
-    if (d.tokens >= (int64_t)TG * 2 * 2 * cus) return launch_tt<TE, 2, EG>(d, x, wr, bias, ids, w, s);
+    if (d.tokens >= (int64_t)TG * 4 * 4 * cus)
+        return launch_tt<TE, 4, EG>(d, x, wr, bias, ids, w, s);
+    if (d.tokens >= (int64_t)TG * 2 * 2 * cus)
+        return launch_tt<TE, 2, EG>(d, x, wr, bias, ids, w, s);
     return launch_tt<TE, 1, EG>(d, x, wr, bias, ids, w, s);
 }
 
@@ -504,10 +526,26 @@ hipError_t launch_lane(const moe_dims &d, const bf16_t *x, const float *wr, cons
     constexpr int STAGE = TPW * RL_HS * 2 + NW * R * G * RL_HS * 4;
     constexpr int PER = STAGE / 1024;
     const int64_t blocks = (d.tokens + TPW - 1) / TPW;
-    route_lane_kernel<G, R, NW, lane_ring(STAGE, PER)>
+    route_lane_kernel<G, R, NW, lane_ring(STAGE, PER), false>
         <<<(unsigned)blocks, 64 * NW + 64, 0, s>>>(x, wr, bias, d.tokens, d.hidden, d.experts,
-                                                   d.top_k, d.renormalize, ids, w);
+                                                   d.top_k, d.renormalize, ids, w, nullptr);
     return hipGetLastError();
+}
+
+// Any number of experts in blocks of NW * R * G per workgroup, logits
+// through z [T][E], then the selection launch (one wave per token).
+template <int G, int R, int NW>
+hipError_t launch_lane_z(const moe_dims &d, const bf16_t *x, const float *wr, const float *bias,
+                         int32_t *ids, float *w, float *z, hipStream_t s) {
+    constexpr int TPW = 64 / R, EP = NW * R * G;
+    constexpr int STAGE = TPW * RL_HS * 2 + EP * RL_HS * 4;
+    constexpr int PER = STAGE / 1024;
+    const dim3 grid((unsigned)((d.tokens + TPW - 1) / TPW), (unsigned)((d.experts + EP - 1) / EP));
+    route_lane_kernel<G, R, NW, lane_ring(STAGE, PER), true><<<grid, 64 * NW + 64, 0, s>>>(
+        x, wr, bias, d.tokens, d.hidden, d.experts, d.top_k, d.renormalize, ids, w, z);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return launch_route_select(d, z, ids, w, s, nullptr);
 }
 
 // Few-token router: one wave per token; lane l runs the chain of expert l.  A chain is H dependent fmas whatever
@@ -816,14 +854,10 @@ hipError_t launch_lane_router(const moe_dims &d, const bf16_t *x, const float *w
     return launch_lane<2, 2, 4>(d, x, wr, bias, ids, w, s);
 }
 
-}  // namespace
-
-namespace {
-// the LDS-DMA of the matrix-core and chain kernels copies 16-byte pieces at
-// 32-bit offsets from a workgroup's first row
-bool route_dma(const moe_dims &d, const bf16_t *x, const float *wr) {
-    return (((uintptr_t)x | (uintptr_t)wr) & 15) == 0 && d.hidden <= kRouteDmaMaxHidden;
-}
+// The matrix-core and chain kernels read x 16 bytes at a time from 16-byte
+// aligned addresses; their LDS-DMA of the router rows takes 16 bytes from any
+// address of a float.
+bool x_aligned(const bf16_t *x) { return ((uintptr_t)x & 15) == 0; }
 // Up to 512 tokens of at most 16 experts: a chain per lane, whose dependent
 // fma is shorter than a quarter of the matrix core's (us, chain against
 // matrix core: Mixtral 64 tokens 16.2 / 21.6, 512 tokens 19.9 / 22.1; DBRX
@@ -831,10 +865,39 @@ bool route_dma(const moe_dims &d, const bf16_t *x, const float *wr) {
 bool route_by_chain(const moe_dims &d) {
     return d.tokens <= kRouteChainMaxTokens && chain_fits(d);
 }
+
+// x at any address of a bf16: the lane-per-token kernel for at most 16
+// experts, and in blocks of 16 experts while the logits have a buffer (up to
+// kRouteLogitsMaxTokens tokens); else the register-tiled kernel.  For 129 to
+// 160 experts below 65536 tokens that takes 32 expert groups of 5, with the
+// most tokens per thread that keeps ~2 waves per SIMD (T / 4096, at most 4):
+// against 16 groups of 10 it reads fewer operands per fma at equal
+// occupancy, or doubles the occupancy of small batches (moe_route, E = 160,
+// H = 5120, us: 64 tokens 272 -> 167, 4096 271 -> 202, 16384 475 -> 410); from
+// 65536 tokens 16 groups of 10 x 4 tokens is faster.
+hipError_t launch_any_alignment(const moe_dims &d, const bf16_t *x, const float *wr,
+                                const float *bias, int32_t *ids, float *w, float *logits,
+                                hipStream_t s) {
+    if (d.experts <= 16) return launch_lane_router(d, x, wr, bias, ids, w, s);
+    if (logits && d.tokens <= kRouteLogitsMaxTokens)
+        return launch_lane_z<2, 2, 4>(d, x, wr, bias, ids, w, logits, s);
+    if (d.experts > 128 && d.experts <= 160 && d.tokens < 65536) {
+        if (d.tokens >= 16384) return launch_tt<5, 4, 32>(d, x, wr, bias, ids, w, s);
+        if (d.tokens >= 8192) return launch_tt<5, 2, 32>(d, x, wr, bias, ids, w, s);
+        return launch_tt<5, 1, 32>(d, x, wr, bias, ids, w, s);
+    }
+    const int te = (d.experts + 15) / 16;
+    if (te <= 2) return launch_te<2>(d, x, wr, bias, ids, w, s);
+    if (te <= 4) return launch_te<4>(d, x, wr, bias, ids, w, s);
+    if (te <= 8) return launch_te<8>(d, x, wr, bias, ids, w, s);
+    if (te <= 10) return launch_te<10>(d, x, wr, bias, ids, w, s);
+    return launch_te<16>(d, x, wr, bias, ids, w, s);
+}
+
 }  // namespace
 
-bool route_dispatches(const moe_dims &d, const bf16_t *x, const float *wr, const float *logits) {
-    if (d.tokens <= 0 || !route_dma(d, x, wr)) return false;
+bool route_dispatches(const moe_dims &d, const bf16_t *x, const float *logits) {
+    if (d.tokens <= 0 || !x_aligned(x)) return false;
     // a chain workgroup is one token, a selection workgroup four
     if (route_by_chain(d)) return d.tokens == 1;
     return d.tokens <= kRouteSelectTokens && mfma_router_selects_apart(d, logits);
@@ -844,20 +907,10 @@ hipError_t launch_route(const moe_dims &d, const bf16_t *x, const float *wr, con
                         int32_t *ids, float *w, float *logits, hipStream_t s,
                         const DispatchOut *disp) {
     if (d.tokens <= 0) return hipSuccess;
-    if (disp && !route_dispatches(d, x, wr, logits)) return hipErrorInvalidValue;
-    if (route_dma(d, x, wr)) {
-        if (route_by_chain(d)) return launch_chain(d, x, wr, bias, ids, w, s, disp);
-        return launch_mfma_router(d, x, wr, bias, ids, w, logits, s, disp);
-    }
-    // any alignment: the lane-per-token kernel, or the register-tiled one
-    // for more than 16 experts
-    if (d.experts <= 16) return launch_lane_router(d, x, wr, bias, ids, w, s);
-    const int te = (d.experts + 15) / 16;
-    if (te <= 2) return launch_te<2>(d, x, wr, bias, ids, w, s);
-    if (te <= 4) return launch_te<4>(d, x, wr, bias, ids, w, s);
-    if (te <= 8) return launch_te<8>(d, x, wr, bias, ids, w, s);
-    if (te <= 10) return launch_te<10>(d, x, wr, bias, ids, w, s);
-    return launch_te<16>(d, x, wr, bias, ids, w, s);
+    if (disp && !route_dispatches(d, x, logits)) return hipErrorInvalidValue;
+    if (!x_aligned(x)) return launch_any_alignment(d, x, wr, bias, ids, w, logits, s);
+    if (route_by_chain(d)) return launch_chain(d, x, wr, bias, ids, w, s, disp);
+    return launch_mfma_router(d, x, wr, bias, ids, w, logits, s, disp);
 }
 
 }  // namespace moe

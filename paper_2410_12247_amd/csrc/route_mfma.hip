@@ -342,15 +342,7 @@ hipError_t launch_mfma_z(const moe_dims &d, const bf16_t *x, const float *wr, co
         x, wr, bias, d.tokens, d.hidden, d.experts, d.top_k, d.renormalize, ids, w, z);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (disp)
-        route_select_kernel<true><<<1, kSelectThreads, 0, s>>>(
-            z, d.tokens, d.experts, d.top_k, d.renormalize, ids, w, *disp);
-    else
-        route_select_kernel<false>
-            <<<(unsigned)((d.tokens + kRouteSelectTokens - 1) / kRouteSelectTokens),
-               kSelectThreads, 0, s>>>(z, d.tokens, d.experts, d.top_k, d.renormalize, ids, w,
-                                       DispatchOut{});
-    return hipGetLastError();
+    return launch_route_select(d, z, ids, w, s, disp);
 }
 
 // Matrix-core router for more than 16 experts.  The time of a launch is its
@@ -390,6 +382,19 @@ int blocks_per_wave(int eb) { return eb > 12 ? 8 : (eb + 1) / 2; }
 // waves of one tile each
 int64_t tile_waves(const moe_dims &d) { return (d.tokens + 15) / 16 * expert_blocks(d); }
 }  // namespace
+
+hipError_t launch_route_select(const moe_dims &d, const float *z, int32_t *ids, float *w,
+                               hipStream_t s, const DispatchOut *disp) {
+    if (disp)
+        route_select_kernel<true><<<1, kSelectThreads, 0, s>>>(
+            z, d.tokens, d.experts, d.top_k, d.renormalize, ids, w, *disp);
+    else
+        route_select_kernel<false>
+            <<<(unsigned)((d.tokens + kRouteSelectTokens - 1) / kRouteSelectTokens),
+               kSelectThreads, 0, s>>>(z, d.tokens, d.experts, d.top_k, d.renormalize, ids, w,
+                                       DispatchOut{});
+    return hipGetLastError();
+}
 
 // Few tokens: the expert blocks over workgroups of their own (logits through
 // the caller's buffer), one tile per wave; a round of a tile per SIMD takes

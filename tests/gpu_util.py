@@ -17,6 +17,15 @@ def dev():
     return torch.device("cuda:0")
 
 
+def off_by(t: torch.Tensor, n: int) -> torch.Tensor:
+    """The same values n elements past a 16-byte boundary."""
+    flat = torch.empty(t.numel() + n, dtype=t.dtype, device=t.device)
+    out = flat[n:].view(t.shape)
+    out.copy_(t)
+    assert flat.data_ptr() % 16 == 0
+    return out
+
+
 def assert_close(got: np.ndarray, ref: np.ndarray, what: str,
                  max_abs: float = MAX_ABS, rel_fro: float = REL_FRO):
     got = np.asarray(got, np.float64)

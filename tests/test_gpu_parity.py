@@ -8,7 +8,8 @@ import torch
 import oracle
 from paper_2410_12247_amd import moe, synth
 
-from gpu_util import Dev, assert_close, assert_guards, bf16, bits, canary_fill, dev, f32, i32
+from gpu_util import (Dev, assert_close, assert_guards, bf16, bits, canary_fill, dev, f32, i32,
+                      off_by)
 
 pytestmark = pytest.mark.gpu
 
@@ -105,20 +106,21 @@ def test_route(name):
     assert weights_match(gw.cpu().numpy(), w)
 
 
+@pytest.mark.parametrize("off", [0, 1])
 @pytest.mark.parametrize("T,E", [(4000, 160), (8192, 160), (12001, 130), (16384, 160),
                                  (20000, 150)])
-def test_route_many_experts_token_tiles(T, E):
-    """The register-tiled router for 129-160 experts takes 1, 2 or 4 tokens
-    per thread by batch size (below 8192, below 16384, from 16384): every band,
-    ragged T and E not a multiple of the 32 expert groups, against the oracle
-    bit for bit."""
+def test_route_many_experts_token_tiles(T, E, off):
+    """129-160 experts, ragged T and E not a multiple of 32, against the oracle
+    bit for bit: the matrix-core router and, with x one element off 16-byte
+    alignment, the register-tiled one, which takes 1, 2 or 4 tokens per thread
+    of 32 expert groups by batch size (below 8192, below 16384, from 16384)."""
     shp = C(name=f"tiles{T}_{E}", index=216, T=T, H=128, I=64, E=E, EL=4, k=6, renorm=False)
     inp = synth.make_inputs(shp, router_only=True)
     _, ids, w = oracle.route(inp.x, inp.w_router, None, shp.k, shp.renorm)
     d = moe.dims(T, shp.H, shp.I, E, shp.k, 0, shp.EL, False)
     gids = torch.empty((T, shp.k), dtype=torch.int32, device=dev())
     gw = torch.empty((T, shp.k), dtype=torch.float32, device=dev())
-    moe.route(d, bf16(inp.x), f32(inp.w_router), None, gids, gw)
+    moe.route(d, off_by(bf16(inp.x), off), f32(inp.w_router), None, gids, gw)
     torch.cuda.synchronize()
     assert np.array_equal(gids.cpu().numpy(), ids)
     assert weights_match(gw.cpu().numpy(), w)
@@ -127,10 +129,10 @@ def test_route_many_experts_token_tiles(T, E):
 @pytest.mark.parametrize("T,E,k", [(777, 256, 8), (2500, 256, 8), (1500, 200, 7)])
 def test_maximum_experts_and_top_k(T, E, k):
     """The supported maximum, 256 experts with top-8 (and a ragged 200 with
-    top-7): the router alone (16 experts per thread) and the whole forward
-    (the lane router in blocks of 16 experts up to 4096 tokens, the
-    combine of eight slots)
-    against the oracle."""
+    top-7): the router alone (every expert in one workgroup) and the whole
+    forward (up to some 2000 tokens the expert blocks in workgroups of their
+    own, logits through the workspace; the combine of eight slots) against
+    the oracle."""
     shp = C(name=f"max{T}_{E}", index=217, T=T, H=192, I=128, E=E, EL=32, e0=E - 40, k=k,
             renorm=True)
     inp = synth.make_inputs(shp)
@@ -160,10 +162,12 @@ def test_maximum_experts_and_top_k(T, E, k):
     (14000, 11, 192, 4, False, True),   # E <= 16 past ~13650 tokens: 4 per lane
     (33, 16, 6144, 4, True, True),      # DBRX's width, one partial workgroup
 ])
-def test_route_lane_shapes(T, E, H, k, renorm, use_bias):
-    """The lane-per-token router (E <= 16) in each of its shapes, picked by
-    expert count and batch size, with ragged token blocks, 1 to 96 stages
-    and the bias, against the oracle bit for bit."""
+@pytest.mark.parametrize("off", [0, 1])
+def test_route_lane_shapes(T, E, H, k, renorm, use_bias, off):
+    """At most 16 experts against the oracle bit for bit, ragged token blocks, 1
+    to 96 stages and the bias: with x one element off 16-byte alignment the
+    lane-per-token router in each of its shapes, picked by expert count and
+    batch size (noted above); aligned, the chain and matrix-core routers."""
     rng = np.random.default_rng(1000 + E + T)
     xb = synth.bf16_bits(rng.standard_normal((T, H), dtype=np.float32))
     wr = rng.standard_normal((E, H), dtype=np.float32) * np.float32(0.02)
@@ -172,7 +176,7 @@ def test_route_lane_shapes(T, E, H, k, renorm, use_bias):
     d = moe.dims(T, H, 64, E, k, renormalize=renorm)
     gids = torch.empty((T, k), dtype=torch.int32, device=dev())
     gw = torch.empty((T, k), dtype=torch.float32, device=dev())
-    moe.route(d, bf16(xb), f32(wr), f32(bias) if use_bias else None, gids, gw)
+    moe.route(d, off_by(bf16(xb), off), f32(wr), f32(bias) if use_bias else None, gids, gw)
     torch.cuda.synchronize()
     assert np.array_equal(gids.cpu().numpy(), ids)
     assert weights_match(gw.cpu().numpy(), w)
@@ -184,7 +188,7 @@ def test_route_lane_shapes(T, E, H, k, renorm, use_bias):
     (33, 16, 6144, 4, True, True),      # DBRX's width, 16 lanes
     (511, 5, 192, 2, False, True),      # three blocks (odd: the pair loop's tail)
     (512, 8, 64, 2, True, False),       # the last batch size on the chain kernel
-    (513, 8, 64, 2, True, False),       # the first on the lane kernel
+    (513, 8, 64, 2, True, False),       # the first on the matrix-core kernel
     (32, 16, 8192, 3, False, False),    # the widest 16-expert row in 64 KB of LDS
     (2, 8, 12288, 2, True, True),       # the widest 8-expert row
 ])
@@ -192,7 +196,7 @@ def test_route_chain_shapes(T, E, H, k, renorm, use_bias):
     """The chain-per-lane router for few tokens (one wave per token, a lane
     per expert, x widened into LDS, router rows through an LDS ring): 1 to
     192 blocks of 64 h, odd block counts, the batch-size boundary with the
-    lane kernel, the widest rows that fit, with the bias, against the
+    matrix-core kernel, the widest rows that fit, with the bias, against the
     oracle bit for bit."""
     rng = np.random.default_rng(2000 + E + T + H)
     xb = synth.bf16_bits(rng.standard_normal((T, H), dtype=np.float32))
@@ -624,15 +628,16 @@ def test_k_split_exact_sums(name):
                                        (1024, 160, True), (1025, 160, False), (64, 32, True),
                                        (33, 256, False), (500, 96, True), (4096, 40, True),
                                        (4097, 40, False)])
-def test_forward_routing_many_experts(T, E, bias):
-    """Routing inside the forward for E > 16: at a few tokens (tokens x
-    expert blocks of 16 up to 512) from the chain-per-lane router, else up
-    to 4096 tokens from the lane-per-token router, both in blocks of 16
-    experts (a ragged last block when 16 does not divide E; 33 tokens leave
-    a ragged token block), through the workspace, and a separate selection;
-    above that from the register-tiled router.  Ids, weights, counts and y match the oracle;
-    duplicated router rows make exact ties, which go to the lower expert
-    index."""
+@pytest.mark.parametrize("off", [0, 1])
+def test_forward_routing_many_experts(T, E, bias, off):
+    """Routing inside the forward for E > 16: few tokens in blocks of 16
+    experts (a ragged last block when 16 does not divide E; 33 tokens leave a
+    ragged token block), logits through the workspace and a separate
+    selection, by the matrix-core router or, with x one element off 16-byte
+    alignment, the lane-per-token router (up to 4096 tokens); above that every
+    expert in one workgroup of the matrix-core or the register-tiled router.
+    Ids, weights, counts and y match the oracle; duplicated router rows make
+    exact ties, which go to the lower expert index."""
     shp = C(name=f"many{T}_{E}", index=214, T=T, H=192, I=64, E=E, EL=4, e0=E - 4, k=6,
             renorm=False)
     inp = synth.make_inputs(shp)
@@ -642,7 +647,9 @@ def test_forward_routing_many_experts(T, E, bias):
     inp.w_router[9] = inp.w_router[3]
     inp.w_router[E - 2] = inp.w_router[E - 3]
     _, ids, w = oracle.route(inp.x, inp.w_router, inp.bias, shp.k, shp.renorm)
-    buf = Dev(inp).forward()
+    g = Dev(inp)
+    g.x = off_by(g.x, off)
+    buf = g.forward()
     assert np.array_equal(buf.topk_ids.cpu().numpy(), ids)
     assert weights_match(buf.topk_w.cpu().numpy(), w)
     counts, *_ = oracle.dispatch(ids, shp.e0, shp.EL)

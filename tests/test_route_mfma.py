@@ -10,7 +10,7 @@ import torch
 
 import oracle
 from paper_2410_12247_amd import moe, synth
-from tests.gpu_util import bf16, dev, f32
+from tests.gpu_util import bf16, dev, f32, off_by
 
 pytestmark = pytest.mark.gpu
 
@@ -98,17 +98,51 @@ def test_nan_logits_pick_distinct_experts(T, E, k, call):
             int((ids == e).sum()) for e in range(E - 3, E)]
 
 
-@pytest.mark.parametrize("E", [40, 160])
-def test_unaligned_rows(E):
-    """x eight bytes off a 16-byte boundary."""
-    T, H, k = 600, 192, 4
+@pytest.mark.parametrize("T,E,off", [
+    (600, 40, 4), (600, 160, 4),  # x eight bytes off: one token per thread, 3 and 32 x 5 experts
+    (600, 100, 2),                # 8 experts per thread
+    (16385, 30, 1),               # two tokens and 2 experts per thread
+    (16384, 250, 1),              # two tokens and 16 experts per thread
+    (65537, 64, 1),               # four tokens and 4 experts per thread
+    (65536, 160, 1),              # four tokens and 10 experts per thread
+])
+def test_unaligned_rows(T, E, off):
+    """x off a 16-byte boundary, more than 16 experts, no logits buffer: the
+    register-tiled kernel."""
+    H, k = 192 if T < 1000 else 64, 4
     xb, wr, bias = draw(T, E, H, True, E)
     _, ids, w = oracle.route(xb, wr, bias, k, True)
-    buf = torch.empty(T * H + 4, dtype=torch.bfloat16, device=dev())
-    x = buf[4:].view(T, H)
-    x.copy_(bf16(xb))
-    assert x.data_ptr() % 16 == 8
-    check(x, f32(wr), f32(bias), ids, w, T, E, H, k, True)
+    check(off_by(bf16(xb), off), f32(wr), f32(bias), ids, w, T, E, H, k, True)
+
+
+@pytest.mark.parametrize("T,E,xoff", [
+    (3, 8, 0), (40, 16, 0),            # a chain per lane
+    (600, 8, 0), (5000, 16, 0),        # matrix cores, at most 16 experts
+    (33, 40, 0), (4097, 160, 0),       # matrix cores, more experts
+    (100, 8, 1), (600, 160, 1),        # x unaligned too: lane per token, register tiles
+])
+def test_unaligned_router(T, E, xoff):
+    """w_router four bytes off a 16-byte boundary."""
+    H, k = 320, 4
+    xb, wr, bias = draw(T, E, H, True, T + E)
+    _, ids, w = oracle.route(xb, wr, bias, k, True)
+    check(off_by(bf16(xb), xoff), off_by(f32(wr), 1), f32(bias), ids, w, T, E, H, k, True)
+
+
+@pytest.mark.parametrize("T", [4, 61])
+def test_unaligned_router_in_the_forward(T):
+    """The same with the logits through the workspace and, at four tokens, the
+    dispatch behind the selection."""
+    E, H, k = 40, 320, 4
+    xb, wr, bias = draw(T, E, H, True, T)
+    _, ids, w = oracle.route(xb, wr, bias, k, True)
+    z = torch.zeros((E, 64, H), dtype=torch.bfloat16, device=dev())
+    buf = moe.MoEBuffers(moe.dims(T, H, 64, E, k, renormalize=True), moe.opts())
+    buf.run(bf16(xb), off_by(f32(wr), 1), f32(bias), z, z, z.view(E, H, 64))
+    torch.cuda.synchronize()
+    assert np.array_equal(buf.topk_ids.cpu().numpy(), ids)
+    np.testing.assert_array_max_ulp(buf.topk_w.cpu().numpy(), w, maxulp=1)
+    assert np.array_equal(buf.counts.cpu().numpy(), np.bincount(ids.ravel(), minlength=E))
 
 
 @pytest.mark.parametrize("E", [8, 16, 17, 160])
