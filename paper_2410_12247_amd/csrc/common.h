@@ -204,6 +204,9 @@ hipError_t launch_dense_down(int64_t rows, int H, int I, const bf16_t *act,
 // token rows over K (mode 0 gate/up, 1 down) on `grid` workgroups, with or
 // without the K split of a partial last round.
 double gemm_launch_us(int mode, int bm, int64_t tiles, int K, int grid, bool split);
+// Share of its rounds of `grid` workgroups that a tiled gate/up launch of
+// `tiles` 128-row tiles over K keeps busy, its last round cut along K.
+double tiled_round_fill(int64_t tiles, int K, int grid);
 // Tiles of one expert of `rows` rows: gate/up N = I (128 act columns per
 // tile), down N = H (256 per tile).
 int64_t gemm_tiles(int mode, int bm, int64_t rows, int N);
@@ -240,9 +243,12 @@ hipError_t launch_skinny_down(const moe_dims &d, int e_first, int e_count,
                               float *y_perm, hipStream_t s);
 // The GEMMs of launches whose experts have at most kStreamMaxRows rows,
 // streaming the weights once with K split over the waves of a workgroup (not
-// the bits of exact order).
+// the bits of exact order).  Where each is faster than the tiled launch:
+// active of the experts are expected to have rows, grid as in
+// gemm_launch_us.
 constexpr int64_t kStreamMaxRows = 16;
-bool stream_fits(int64_t max_rows, int H, int I);
+bool stream_gateup_fits(int64_t max_rows, double active, int experts, int H, int I, int grid);
+bool stream_down_fits(int64_t max_rows, double active, int experts, int H, int I);
 hipError_t launch_stream_gateup(const moe_dims &d, int e_first, int e_count,
                                 const int32_t *offsets, const bf16_t *x, const int32_t *row_map,
                                 const bf16_t *w_gate, const bf16_t *w_up, bf16_t *act,

@@ -742,20 +742,25 @@ moe_status forward_impl(const moe_dims &d, const moe_opts &opt, const moe_bf16 *
                         : group_launch_rows(stage_max_rows, need_counts ? &hc[b0] : nullptr,
                                             per_stage, t_hi - t_lo, (double)d.top_k / d.experts,
                                             H, I, grid, split);
-                // Few rows per expert: the streaming form (the down GEMM's
-                // skinny tile where it has tiles enough).  Not beside a
-                // shared FFN, whose workgroups then wait for the many small
-                // ones (DeepSeekV2 8 / 16 tokens 120 / 143 us without, 129 /
-                // 153 with; Mixtral 1 / 8 tokens 72 / 154 -> 62 / 146, DBRX
-                // 8 / 16 tokens 174 / 198 -> 160 / 189).  A forced tile
-                // height or CU budget is the tiled launch's.
+                // Few rows per expert: the streaming forms where they are
+                // faster (the down GEMM's skinny tile first, where it has
+                // tiles enough).  Not beside a shared FFN, whose workgroups
+                // then wait for the many small ones (DeepSeekV2 8 / 16 tokens
+                // 120 / 143 us without, 129 / 153 with).  A forced tile height
+                // or CU budget is the tiled launch's.
                 const bool stream = split && !has_shared && o->group_tile_rows == 0 &&
-                                    o->gemm_cu_budget == 0 && o->side_cus == 0 &&
-                                    stream_fits(stage_max_rows, H, I);
+                                    o->gemm_cu_budget == 0 && o->side_cus == 0;
                 const int64_t active =
                     std::min<int64_t>(per_stage, (t_hi - t_lo) * (int64_t)d.top_k);
+                // experts with rows: counted, or expected under uniform routing
+                const double active_mean =
+                    need_counts ? (double)std::count_if(&hc[b0], &hc[b0] + per_stage,
+                                                        [](int32_t n) { return n > 0; })
+                                : per_stage * (1.0 - std::pow(1.0 - (double)d.top_k / d.experts,
+                                                              (double)(t_hi - t_lo)));
                 MOE_TRY(tm.begin(sr, PH_GATEUP));
-                if (stream)
+                if (stream &&
+                    stream_gateup_fits(stage_max_rows, active_mean, per_stage, H, I, grid))
                     MOE_HIP(launch_stream_gateup(d, e_w, per_stage, goff, xrows, rmap, w_gate,
                                                  w_up, act, sr));
                 else
@@ -765,7 +770,8 @@ moe_status forward_impl(const moe_dims &d, const moe_opts &opt, const moe_bf16 *
                 MOE_TRY(tm.begin(sr, PH_DOWN));
                 if (skinny_down_fits(stage_max_rows, active, H, I))
                     MOE_HIP(launch_skinny_down(d, e_w, per_stage, goff, act, w_down, y_perm, sr));
-                else if (stream)
+                else if (stream &&
+                         stream_down_fits(stage_max_rows, active_mean, per_stage, H, I))
                     MOE_HIP(launch_stream_down(d, e_w, per_stage, goff, act, w_down, y_perm, sr));
                 else
                     MOE_HIP(launch_group_down(d, e_w, per_stage, goff, act, w_down, y_perm, grid,

@@ -1254,7 +1254,26 @@ const TileCost &tile_cost(int bm) {
     return kTileCosts[0];
 }
 
+// Equal K pieces that group_kernel cuts the rem tiles of a partial last round
+// into, after full_rounds whole ones, nk K stages each.
+int split_pieces(int64_t rem, int64_t full_rounds, int nk, int grid) {
+    if (2 * rem > grid) return 1;
+    return (int)std::max<int64_t>(
+        1, std::min<int64_t>(
+               std::min<int64_t>(kSplitMaxPieces, grid / rem),
+               std::min<int64_t>(nk / (full_rounds == 0 ? kSplitMinStagesAlone : kSplitMinStages),
+                                 kSplitSlots / rem)));
+}
+
 }  // namespace
+
+double tiled_round_fill(int64_t tiles, int K, int grid) {
+    if (tiles <= 0) return 0.0;
+    const int64_t full = tiles / grid, rem = tiles % grid;
+    double rounds = (double)full;
+    if (rem > 0) rounds += 1.0 / split_pieces(rem, full, K / pp_stage_k(128), grid);
+    return (double)tiles / (grid * rounds);
+}
 
 double gemm_launch_us(int mode, int bm, int64_t tiles, int K, int grid, bool split) {
     if (tiles <= 0) return 0.0;
@@ -1269,14 +1288,8 @@ double gemm_launch_us(int mode, int bm, int64_t tiles, int K, int grid, bool spl
         // (a round of more than half the grid that the kernel spreads
         // stream-K, for tall tiles at most half full, is priced unsplit: an
         // upper bound)
-        int S = 1;
-        if (split && 2 * rem <= grid) {
-            S = (int)std::min<int64_t>(
-                std::min<int64_t>(kSplitMaxPieces, grid / rem),
-                std::min<int64_t>(nk / (full_rounds == 0 ? kSplitMinStagesAlone : kSplitMinStages),
-                                  kSplitSlots / rem));
-        }
-        const double busy = (double)std::min<int64_t>(grid, rem * std::max(S, 1)) / grid;
+        const int S = split ? split_pieces(rem, full_rounds, nk, grid) : 1;
+        const double busy = (double)std::min<int64_t>(grid, rem * S) / grid;
         const double part = kPartialRound[md] + (1.0 - kPartialRound[md]) * busy;
         if (S >= 2)
             us += loop_us / S * part + c.epi_us[md] + kFixupUs[md] +

@@ -5,10 +5,15 @@
 // flight, loaded straight into registers in the MFMA's operand layout (no LDS
 // and no barrier while the weights stream).  The waves' partial sums meet in
 // LDS, are added in wave order (the same bits on every run) and the epilogue
-// is applied there.  Forward, us, tiled GEMM with a K split and its fix-up
-// launch -> this: Mixtral 1 token 78.5 -> 69.3, 13 tokens 163.8 -> 153.8;
-// DBRX 8 tokens 174 -> 160; 64 experts of 2048 x 1024, 1 token 70 -> 55.
+// is applied there.  Against the tiled GEMM with a K split and its fix-up
+// launch it saves the fix-up and the tiles' padding; its weight stream itself
+// is no faster, so it runs where one of those weighs (stream_gateup_fits,
+// stream_down_fits).  Forward, us, mean of four placements of the weights in
+// memory, tiled -> this: Mixtral 1 token 70 -> 61, 4 tokens 125 -> 117; DBRX 1
+// token 86 -> 78, 8 tokens 189 -> 181; 64 experts of 2048 x 1024, 1 token 59
+// -> 54.
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "common.h"
@@ -17,6 +22,8 @@ namespace moe {
 namespace {
 
 constexpr int SW = 8;  // waves of a workgroup (pieces of K)
+// steps of 32 K in flight per wave: gate/up; down over a short and a long K
+constexpr int kGateupSteps = 8, kShortSteps = 6, kLongSteps = 12;
 constexpr int kStreamBufferFlags = 0x00020000;
 
 __device__ __forceinline__ uint32_t pack2(float a, float b) {
@@ -163,9 +170,43 @@ hipError_t launch(const int32_t *offsets, int e_first, int e_count, const bf16_t
 
 }  // namespace
 
-bool stream_fits(int64_t max_rows, int H, int I) {
-    // one fragment of rows; 32-bit byte offsets into 16 weight rows
-    return max_rows <= kStreamMaxRows && H <= (1 << 20) && I <= (1 << 20);
+// Both rules count workgroups per compute unit, two of which are resident;
+// every time here is a mean over four placements of the weights in memory.
+//
+// Gate/up, us, tiled -> streamed.  Every expert has its workgroups, whether it
+// has rows or not, and with many experts the empty ones cost more than is
+// saved (256 experts of 2048 x 2048, 1 token: 34 -> 47).  A small launch, most
+// of it resident at once, gains by the missing fix-up: up to 3 1/4 workgroups
+// per unit where a wave's piece of K is whole rounds of its steps in flight or
+// K is at most one round (4096 x 3584: 33 -> 28 at 448 workgroups, 46 -> 44 at
+// 740; 2048 x 1408: 29 -> 26 at 680), else up to 1 1/4 (5120 x 1536, whose 20
+// steps take the time of 24: 27 -> 23 at 200, 44 -> 48 at 580).  A larger one
+// gains while the tiled launch leaves units idle (6144 x 1344: 62% full 112 ->
+// 105, 94% 96 -> 86; 6144 x 2688, 98%: 61 -> 64), in whole rounds of K and,
+// where K is one round and a workgroup soon done, at most 16 of them per unit
+// (60 experts of 2048 x 1408, 21 per unit, 6 tokens 48 -> 57; 8 of 4096 x
+// 14336, 28 per unit, 6 tokens 328 -> 285).
+bool stream_gateup_fits(int64_t max_rows, double active, int experts, int H, int I, int grid) {
+    constexpr int ROUND = 32 * SW * kGateupSteps, MAX_H = 2 * ROUND;
+    const double cus = device_cu_count();
+    const double per_cu = experts * (I / 16) / cus, live = active * (I / 16) / cus;
+    if (max_rows > kStreamMaxRows || per_cu > 32.0) return false;
+    const bool whole = H % ROUND == 0;
+    if (live <= (H <= ROUND || (whole && H <= MAX_H) ? 3.25 : 1.25)) return true;
+    const int64_t tiles = std::llround(active * ((I + 127) / 128));
+    return whole && (H > ROUND || per_cu <= 16.0) && tiled_round_fill(tiles, H, grid) < 0.95;
+}
+
+// Down (where the skinny tile does not apply): one workgroup per unit, where
+// the tiled launch needs its K split to fill the chip (us, tiled -> streamed:
+// 4096 x 3584 22 -> 18 at 256 workgroups, 29 -> 31 at 420), or three where a
+// wave's whole piece of K is in flight (2048 x 1408, 60 experts: 22 -> 16 at
+// 490, 24 -> 21 at 700).
+bool stream_down_fits(int64_t max_rows, double active, int experts, int H, int I) {
+    const double cus = device_cu_count();
+    const double per_cu = experts * (H / 32) / cus, live = active * (H / 32) / cus;
+    return max_rows <= kStreamMaxRows && per_cu <= 32.0 &&
+           live <= (I <= 32 * SW * kShortSteps ? 3.0 : 1.0);
 }
 
 hipError_t launch_stream_gateup(const moe_dims &d, int e_first, int e_count,
@@ -173,7 +214,7 @@ hipError_t launch_stream_gateup(const moe_dims &d, int e_first, int e_count,
                                 const bf16_t *w_gate, const bf16_t *w_up, bf16_t *act,
                                 hipStream_t s) {
     if (e_count <= 0) return hipSuccess;
-    return launch<0, 2, 8>(offsets, e_first, e_count, x, row_map, d.top_k, w_gate, w_up,
+    return launch<0, 2, kGateupSteps>(offsets, e_first, e_count, x, row_map, d.top_k, w_gate, w_up,
                            (int64_t)d.inter * d.hidden, d.inter, d.hidden, act, s);
 }
 
@@ -183,11 +224,11 @@ hipError_t launch_stream_down(const moe_dims &d, int e_first, int e_count,
     if (e_count <= 0) return hipSuccess;
     const int64_t wstride = (int64_t)d.hidden * d.inter;
     // a wave's whole piece of K in flight where it is short
-    if (d.inter <= 32 * SW * 6)
-        return launch<1, 2, 6>(offsets, e_first, e_count, act, nullptr, 1, w_down, nullptr,
-                               wstride, d.hidden, d.inter, y, s);
-    return launch<1, 2, 12>(offsets, e_first, e_count, act, nullptr, 1, w_down, nullptr, wstride,
-                            d.hidden, d.inter, y, s);
+    if (d.inter <= 32 * SW * kShortSteps)
+        return launch<1, 2, kShortSteps>(offsets, e_first, e_count, act, nullptr, 1, w_down,
+                                         nullptr, wstride, d.hidden, d.inter, y, s);
+    return launch<1, 2, kLongSteps>(offsets, e_first, e_count, act, nullptr, 1, w_down, nullptr,
+                                    wstride, d.hidden, d.inter, y, s);
 }
 
 }  // namespace moe

@@ -97,6 +97,9 @@ def test_skinny_heights_mixed():
     (320, 192),     # ten and six steps over eight waves
     (1344, 576),    # uneven pieces, more steps than are in flight
     (576, 2112),    # the deep ring of the down GEMM
+    (2304, 64),     # gate/up: nine steps per wave, eight in flight
+    (4096, 128),    # sixteen
+    (256, 3584),    # down: fourteen steps per wave, twelve in flight
 ])
 def test_stream_gemms(T, H, I):
     """The forward of a few tokens without shared experts: both GEMMs stream
