@@ -244,7 +244,8 @@ moe_status moe_ffn_group(const moe_dims *dims, int32_t e_first, int32_t e_count,
     // decode-sized experts with enough tiles: the skinny down tile
     const int64_t active = std::min<int64_t>(e_count, dims->tokens * dims->top_k);
     if (skinny_down_fits(dims->tokens, active, dims->hidden, dims->inter))
-        MOE_HIP(launch_skinny_down(*dims, e_first, e_count, offsets, act, w_down, y_perm, s));
+        MOE_HIP(launch_skinny_down(*dims, e_first, e_count, offsets, act, w_down, y_perm,
+                                   dims->tokens, active, s));
     else
         MOE_HIP(launch_group_down(*dims, e_first, e_count, offsets, act, w_down, y_perm, grid,
                                   nullptr, nullptr, bm, s));

@@ -240,7 +240,8 @@ constexpr int64_t kSkinnyMaxRows = 64;
 bool skinny_down_fits(int64_t max_rows, int64_t active_experts, int N, int K);
 hipError_t launch_skinny_down(const moe_dims &d, int e_first, int e_count,
                               const int32_t *offsets, const bf16_t *act, const bf16_t *w_down,
-                              float *y_perm, hipStream_t s);
+                              float *y_perm, int64_t max_rows, int64_t active_experts,
+                              hipStream_t s);
 // The GEMMs of launches whose experts have at most kStreamMaxRows rows,
 // streaming the weights once with K split over the waves of a workgroup (not
 // the bits of exact order).  Where each is faster than the tiled launch:

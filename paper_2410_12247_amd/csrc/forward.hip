@@ -769,7 +769,8 @@ moe_status forward_impl(const moe_dims &d, const moe_opts &opt, const moe_bf16 *
                 MOE_TRY(tm.end(sr));
                 MOE_TRY(tm.begin(sr, PH_DOWN));
                 if (skinny_down_fits(stage_max_rows, active, H, I))
-                    MOE_HIP(launch_skinny_down(d, e_w, per_stage, goff, act, w_down, y_perm, sr));
+                    MOE_HIP(launch_skinny_down(d, e_w, per_stage, goff, act, w_down, y_perm,
+                                               stage_max_rows, active, sr));
                 else if (stream &&
                          stream_down_fits(stage_max_rows, active_mean, per_stage, H, I))
                     MOE_HIP(launch_stream_down(d, e_w, per_stage, goff, act, w_down, y_perm, sr));

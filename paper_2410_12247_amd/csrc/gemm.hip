@@ -953,8 +953,9 @@ template <int MODE> using GroupTile = TileOf<MODE>;
 // height for the launch -> per expert: DeepSeekV2 61 tokens 62 -> 51, DBRX 64
 // 50.9 -> 49.0, 64 tokens over 64 experts of 2048 x 1024 20.5 -> 19.3).
 // Weight and act rows stream through a ring of LDS stages of SK_BK K by
-// LDS-DMA, all but one stage ahead, as many stages as 64 KB of LDS hold, the
-// 16-byte chunks of each row XOR-placed as in the ping-pong tile.  The MFMA (16x16x32 bf16, the weight fragment as the A
+// LDS-DMA, all but one stage ahead, as many stages as the launch's LDS holds
+// (sk_ring), the 16-byte chunks of each row XOR-placed as in the ping-pong
+// tile.  The MFMA (16x16x32 bf16, the weight fragment as the A
 // operand, K ascending from 0) and the fragment contents are the ping-pong
 // tile's, so the outputs carry the same bits as every other tile height in
 // exact order.  The fragment reads and their wait are one assembly block:
@@ -981,12 +982,19 @@ __host__ __device__ constexpr int sk_lps(int bm, int bk) { return (SK_BN + bm) *
 __host__ __device__ constexpr size_t sk_lds_bytes(int bm, int bk, int ns) {
     return (size_t)ns * (SK_BN + bm) * bk * 2 + (size_t)(4 - bm / 16) * 16 * bk * 2;
 }
-// stages of a tile of bm rows in SK_LDS_MAX, as many as vmcnt can count
-__host__ __device__ constexpr int sk_ring(int bm, int bk) {
+// stages of a tile of bm rows in `lds` bytes, as many as vmcnt can count
+__host__ __device__ constexpr int sk_ring(int bm, int bk, size_t lds) {
     int ns = sk_ahead_max(sk_lps(bm, bk)) + 1;
-    while (sk_lds_bytes(bm, bk, ns) > SK_LDS_MAX) --ns;
+    while (ns > 1 && sk_lds_bytes(bm, bk, ns) > lds) --ns;
     return ns;
 }
+// LDS of a launch's workgroups: SK_LDS_MAX, two resident per compute unit;
+// or, three resident, four stages of up to 32 rows, where every tile that may
+// have rows is then resident at once.  us, two -> three: 700 tiles (2.7 per
+// unit) of 6144 x 1344 28.0 -> 26.4, of 6144 x 10752 176 -> 161; but 3.6 per
+// unit of 4096 x 6400 132 -> 160.
+constexpr size_t SK_LDS_THREE = sk_lds_bytes(32, 64, 4);
+static_assert(3 * SK_LDS_THREE <= 160 * 1024, "three resident");
 
 // one K-step's fragments: 4 weight fragments from wa, 4 act fragments from
 // xa (a tile of fewer rows reads the first ones; the others land in the
@@ -1119,10 +1127,10 @@ __device__ __forceinline__ void skinny_tile(bf16_t *smem, int ns, int r0, int ro
 // the r < rows of expert e (offsets indexed by e_first + e, as in the other
 // launches); grid = e_count * (N / SK_BN).  The expert's rows, read on the
 // device, pick the tile's height (every expert's may be far below the
-// launch's bound, the tokens), and the ring takes what SK_LDS_MAX holds:
-// against one height for the launch, us, DeepSeekV2 61 tokens 62 -> 51, Zipf
-// 64 tokens 20.5 -> 19.3, DBRX 64 tokens 50.9 -> 49.0.
-template <int BK>
+// launch's bound, the tokens): against one height for the launch, us,
+// DeepSeekV2 61 tokens 62 -> 51, Zipf 64 tokens 20.5 -> 19.3, DBRX 64 tokens
+// 50.9 -> 49.0.
+template <int BK, size_t LDS>
 __global__ __launch_bounds__(64) void skinny_down_kernel(const int32_t *__restrict__ offsets,
                                                          int e_first, int e_count,
                                                          const bf16_t *__restrict__ act,
@@ -1139,11 +1147,11 @@ __global__ __launch_bounds__(64) void skinny_down_kernel(const int32_t *__restri
     if (rows <= 0) return;  // (rows <= 64: the launcher's bound)
     const bf16_t *we = w + (int64_t)(e_first + e) * wstride;
     if (rows <= 16)
-        skinny_tile<16, BK>(smem, sk_ring(16, BK), r0, rows, n0, act, we, N, K, y);
+        skinny_tile<16, BK>(smem, sk_ring(16, BK, LDS), r0, rows, n0, act, we, N, K, y);
     else if (rows <= 32)
-        skinny_tile<32, BK>(smem, sk_ring(32, BK), r0, rows, n0, act, we, N, K, y);
+        skinny_tile<32, BK>(smem, sk_ring(32, BK, LDS), r0, rows, n0, act, we, N, K, y);
     else
-        skinny_tile<64, BK>(smem, sk_ring(64, BK), r0, rows, n0, act, we, N, K, y);
+        skinny_tile<64, BK>(smem, sk_ring(64, BK, LDS), r0, rows, n0, act, we, N, K, y);
 }
 
 int round_grid(int64_t tiles) { return (int)(((tiles + NXCD - 1) / NXCD) * NXCD); }
@@ -1462,13 +1470,21 @@ bool skinny_down_fits(int64_t max_rows, int64_t active_experts, int N, int K) {
 
 hipError_t launch_skinny_down(const moe_dims &d, int e_first, int e_count,
                               const int32_t *offsets, const bf16_t *act, const bf16_t *w_down,
-                              float *y_perm, hipStream_t s) {
+                              float *y_perm, int64_t max_rows, int64_t active_experts,
+                              hipStream_t s) {
     if (e_count <= 0) return hipSuccess;
     const int N = d.hidden, K = d.inter;
-    if (N % SK_BN || K % SK_BK) return hipErrorInvalidValue;
-    static_assert(sk_ring(64, SK_BK) >= 2 && sk_ring(16, SK_BK) >= 2, "ring depth");
-    skinny_down_kernel<SK_BK><<<(unsigned)(e_count * (N / SK_BN)), 64, SK_LDS_MAX, s>>>(
-        offsets, e_first, e_count, act, w_down, (int64_t)N * K, N, K, y_perm);
+    if (N % SK_BN || K % SK_BK || max_rows > kSkinnyMaxRows) return hipErrorInvalidValue;
+    static_assert(sk_ring(64, SK_BK, SK_LDS_THREE) >= 2, "ring depth");
+    const int64_t active = std::min<int64_t>(e_count, std::max<int64_t>(1, active_experts));
+    const int64_t tiles = active * (N / SK_BN), cus = device_cu_count();
+    const unsigned blocks = (unsigned)(e_count * (N / SK_BN));
+    if (max_rows <= 32 && tiles > 2 * cus && tiles <= 3 * cus)
+        skinny_down_kernel<SK_BK, SK_LDS_THREE><<<blocks, 64, SK_LDS_THREE, s>>>(
+            offsets, e_first, e_count, act, w_down, (int64_t)N * K, N, K, y_perm);
+    else
+        skinny_down_kernel<SK_BK, SK_LDS_MAX><<<blocks, 64, SK_LDS_MAX, s>>>(
+            offsets, e_first, e_count, act, w_down, (int64_t)N * K, N, K, y_perm);
     return hipGetLastError();
 }
 

@@ -70,16 +70,21 @@ def test_dense_tiles(rows, H, I):
     assert bool(((y[:rows].double() - want).abs() <= bound).all())
 
 
-def test_skinny_heights_mixed():
+@pytest.mark.parametrize("I", [64, 128, 1024])
+@pytest.mark.parametrize("rows", [
+    [0, 1, 16, 17, 32, 33, 64],
+    [0, 1, 2, 15, 16, 17, 32],  # at most 32: three workgroups resident per compute unit
+])
+def test_skinny_heights_mixed(rows, I):
     """One decode launch whose experts have 0 to 64 rows: each expert's rows
-    pick the height of its down tiles."""
-    rows = [0, 1, 16, 17, 32, 33, 64]
-    H, I, E, R = 4736, 128, len(rows), sum(rows)  # 7 x 74 tiles: at least two per compute unit
+    pick the height of its down tiles; K of fewer stages than the ring and of
+    more."""
+    H, E, R = 4736, len(rows), sum(rows)  # 7 x 74 tiles: two to three per compute unit
     rng = np.random.default_rng(5)
     off = torch.from_numpy(np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)).to(dev())
     x = ints(rng, R, H)
     wg, wu, wd = ints(rng, E, I, H), ints(rng, E, I, H), ints(rng, E, H, I)
-    d = moe.dims(64, H, I, 8, 8, 0, E, True)
+    d = moe.dims(max(rows), H, I, 8, 8, 0, E, True)
     act = torch.zeros((R, I), dtype=torch.bfloat16, device=dev())
     y = torch.full((R + 1, H), 7.0, device=dev())
     moe.ffn_group(d, 0, E, off, x, wg, wu, wd, act, y[:R])
