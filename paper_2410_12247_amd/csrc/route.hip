@@ -692,6 +692,13 @@ __device__ __forceinline__ void route_chain(char *lds, const bf16_t *__restrict_
     const int e = lane;
     const bool live = lane < 4 * NQ && e < E;
     const int nb = H / 64;
+    // 9 to 16 experts: kernel arguments used after the loop are loaded here.
+    // Scalar loads return out of order, so one left in flight turns the first
+    // LDS wait of every ring turn into a wait for all reads (H = 6144, us: 64
+    // tokens 26.9 -> 25.4, 300 tokens 31.3 -> 26.8).  Up to 8 experts it
+    // measures the other way round (H = 4096, 64 tokens: 17.4 loaded here,
+    // 16.5 left to the compiler).
+    if constexpr (NQ == 4) asm volatile("" ::"s"(ids), "s"(wout));
 
     // DMA: request q of a block moves rows 4q .. 4q + 3 (lane l: row 4q +
     // l / 16 at position l % 16, i.e. chunk (l % 16) ^ (row % 16)); rows
