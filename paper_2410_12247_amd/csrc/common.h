@@ -142,6 +142,9 @@ bool route_dispatches(const moe_dims &d, const bf16_t *x, const float *logits);
 hipError_t launch_mfma_router(const moe_dims &d, const bf16_t *x, const float *wr,
                               const float *bias, int32_t *ids, float *w, float *logits,
                               hipStream_t s, const DispatchOut *disp);
+// The tests' view of its workgroup shape for more than 16 experts (host only):
+// returns the tokens, *blocks the expert blocks per wave.
+extern "C" int32_t moe_router_shape_for_tests(const moe_dims *d, int32_t *blocks);
 // Whether launch_mfma_router sends the logits through their buffer to a
 // selection launch (four tokens per workgroup).
 bool mfma_router_selects_apart(const moe_dims &d, const float *logits);

@@ -351,11 +351,24 @@ hipError_t launch_mfma_z(const moe_dims &d, const bf16_t *x, const float *wr, co
 // and selection (measured at E = 160: 3 tiles 69 us, 5 tiles 113, 10 tiles
 // 200-205, 20 tiles 387); the shape with the lowest cost runs.  A shape
 // trades operand reads per MFMA (more tiles per wave) and tokens per
-// workgroup against compute units left idle.
+// workgroup against compute units left idle.  A tile's time is proportional
+// to H and the start is not; the rule keeps the two figures of H = 5120 at
+// every width (only the choice of shape depends on them).
 constexpr int ring_slots(int stage) { return 3 * stage <= 160 * 1024 ? 3 : 2; }
 double mfma_cost(int64_t tokens, int tok, int tiles) {
     const int64_t per_round = (int64_t)tok * device_cu_count();
     return (double)((tokens + per_round - 1) / per_round) * (20.0 * tiles + 10.0);
+}
+// Tokens of a workgroup (16, 32, 64 or 128; the largest of equal cost) with te
+// expert blocks per wave where two waves share the experts; 16 tokens spread
+// them over four.
+int mfma_tokens(int64_t tokens, int te) {
+    const int tiles[4] = {(te + 1) / 2, te, 2 * te, 4 * te};
+    int best = 0;
+    for (int i = 1; i < 4; ++i)
+        if (mfma_cost(tokens, 16 << i, tiles[i]) <= mfma_cost(tokens, 16 << best, tiles[best]))
+            best = i;
+    return 16 << best;
 }
 template <int TT, int TE, int TW, int EW>
 hipError_t launch_mfma_ring(const moe_dims &d, const bf16_t *x, const float *wr,
@@ -367,14 +380,12 @@ hipError_t launch_mfma_ring(const moe_dims &d, const bf16_t *x, const float *wr,
 template <int TE>
 hipError_t launch_mfma_te(const moe_dims &d, const bf16_t *x, const float *wr, const float *bias,
                           int32_t *ids, float *w, hipStream_t s) {
-    constexpr int TE4 = (TE + 1) / 2;  // over four waves
-    const double c16 = mfma_cost(d.tokens, 16, TE4), c32 = mfma_cost(d.tokens, 32, TE);
-    const double c64 = mfma_cost(d.tokens, 64, 2 * TE), c128 = mfma_cost(d.tokens, 128, 4 * TE);
-    const double best = std::min(std::min(c16, c32), std::min(c64, c128));
-    if (c128 == best) return launch_mfma_ring<2, TE, 4, 2>(d, x, wr, bias, ids, w, s);
-    if (c64 == best) return launch_mfma_ring<1, TE, 4, 2>(d, x, wr, bias, ids, w, s);
-    if (c32 == best) return launch_mfma_ring<1, TE, 2, 2>(d, x, wr, bias, ids, w, s);
-    return launch_mfma_ring<1, TE4, 1, 4>(d, x, wr, bias, ids, w, s);
+    switch (mfma_tokens(d.tokens, TE)) {
+        case 128: return launch_mfma_ring<2, TE, 4, 2>(d, x, wr, bias, ids, w, s);
+        case 64: return launch_mfma_ring<1, TE, 4, 2>(d, x, wr, bias, ids, w, s);
+        case 32: return launch_mfma_ring<1, TE, 2, 2>(d, x, wr, bias, ids, w, s);
+        default: return launch_mfma_ring<1, (TE + 1) / 2, 1, 4>(d, x, wr, bias, ids, w, s);
+    }
 }
 // expert blocks, and per wave with the experts over two waves (1 .. 6 or 8)
 int expert_blocks(const moe_dims &d) { return (d.experts + 15) / 16; }
@@ -408,6 +419,12 @@ bool mfma_router_selects_apart(const moe_dims &d, const float *logits) {
     const double cz = (double)((tile_waves(d) + simds - 1) / simds) * 20.0 + 10.0;
     return cz <= std::min(mfma_cost(d.tokens, 16, (eb + 3) / 4),
                           mfma_cost(d.tokens, 32, blocks_per_wave(eb)));
+}
+
+extern "C" int32_t moe_router_shape_for_tests(const moe_dims *d, int32_t *blocks) {
+    const int te = blocks_per_wave(expert_blocks(*d)), tok = mfma_tokens(d->tokens, te);
+    *blocks = tok == 16 ? (te + 1) / 2 : te;
+    return tok;
 }
 
 hipError_t launch_mfma_router(const moe_dims &d, const bf16_t *x, const float *wr,
