@@ -22,7 +22,7 @@
  *   failure on the calling thread.  Nothing aborts or throws.
  * - tokens == 0 is a valid no-op.
  * - Supported sizes: 1 <= experts <= 256, 1 <= top_k <= min(experts, 8),
- *   hidden, inter and shared_inter multiples of 64, local experts
+ *   hidden, inter and shared_inter multiples of 64 up to 2^20, local experts
  *   [local_begin, local_begin + local_count) inside [0, experts),
  *   tokens * top_k < 2^31.
  * - Results are deterministic: the same inputs and options give the same
@@ -30,9 +30,11 @@
  *   moe_ffn_dense) every expert-GEMM output is one pass over K, so the bits
  *   are also the same for any pipeline number, stage kind, CU budget and
  *   either GEMM kind.  Without it the grouped GEMM may cut the tiles of its
- *   last, partial round, or every tile of a launch of few rows per expert,
- *   into K pieces summed in a fixed order, which moves the last bits of
- *   those outputs with the launch's tile count.
+ *   last, partial round into K pieces summed in a fixed order, and a launch
+ *   of at most 16 rows per expert may run as a streaming GEMM that cuts every
+ *   K into eight; which of them it does, and so the last bits, follows from
+ *   the shape and the options (group_tile_rows, gemm_cu_budget or side_cus
+ *   other than 0 switch the streaming form off).
  */
 #ifndef MOE_H
 #define MOE_H
@@ -362,7 +364,9 @@ moe_status moe_pipeline_plan(const moe_dims *dims, const moe_opts *opts, const i
  * prices each launch from measured per-tile costs of every tile height:
  * GroupGemm is one launch over the stage with one tile height (the model's
  * cheapest up to the smallest height that holds the largest expert, taken
- * when at least 5% below that height's price; or opts->group_tile_rows);
+ * when at least 5% below that height's price; or opts->group_tile_rows), also
+ * where a decode-sized launch would take the streaming or the one-wave form,
+ * which the model does not know;
  * DenseGemm is one launch per expert with its own tile height.  Writes *dense (1 when
  * the stage would run DenseGemm under opts->gemm_mode, AUTO included) and,
  * when not NULL, tile_rows[e] (the tile height of expert e's launch, 0 for

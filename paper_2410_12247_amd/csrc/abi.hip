@@ -44,7 +44,7 @@ moe_status check_dims(const moe_dims *d) {
     if (d->inter <= 0 || d->inter % kDimAlign)
         return fail(MOE_ERR_INVALID, "inter %d not a positive multiple of %d", d->inter,
                     kDimAlign);
-    if (d->hidden > (1 << 20) || d->inter > (1 << 20) || d->shared_inter > (1 << 20))
+    if (d->hidden > kMaxWidth || d->inter > kMaxWidth || d->shared_inter > kMaxWidth)
         return fail(MOE_ERR_INVALID, "hidden/inter above 2^20");
     if (d->local_begin < 0 || d->local_count < 1 ||
         d->local_begin + d->local_count > d->experts)
@@ -243,7 +243,7 @@ moe_status moe_ffn_group(const moe_dims *dims, int32_t e_first, int32_t e_count,
                                 act, grid, nullptr, nullptr, bm, s));
     // decode-sized experts with enough tiles: the skinny down tile
     const int64_t active = std::min<int64_t>(e_count, dims->tokens * dims->top_k);
-    if (skinny_down_fits(dims->tokens, active, dims->hidden, dims->inter))
+    if (skinny_down_fits(dims->tokens, active, dims->hidden))
         MOE_HIP(launch_skinny_down(*dims, e_first, e_count, offsets, act, w_down, y_perm,
                                    dims->tokens, active, s));
     else
@@ -257,7 +257,7 @@ moe_status moe_ffn_dense(int64_t rows, int32_t hidden, int32_t inter, const moe_
                          const moe_bf16 *w_down, moe_bf16 *act, float *y, void *stream) {
     if (rows < 0) return fail(MOE_ERR_INVALID, "moe_ffn_dense: rows < 0");
     if (hidden <= 0 || hidden % kDimAlign || inter <= 0 || inter % kDimAlign ||
-        hidden > (1 << 20) || inter > (1 << 20))
+        hidden > kMaxWidth || inter > kMaxWidth)
         return fail(MOE_ERR_INVALID, "moe_ffn_dense: hidden %d / inter %d not multiples of %d",
                     hidden, inter, kDimAlign);
     if (rows == 0) return MOE_OK;

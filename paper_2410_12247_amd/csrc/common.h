@@ -19,6 +19,9 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kMaxExperts = 256;
 constexpr int kMaxTopK = 8;
 constexpr int kDimAlign = 64;  // hidden / inter multiple
+// Widest hidden / inter / shared_inter: the kernels' 32-bit byte offsets reach
+// 320 fp32 rows of it.
+constexpr int32_t kMaxWidth = 1 << 20;
 
 // Records `msg` as the calling thread's last error and returns `s`.
 moe_status fail(moe_status s, const char *fmt, ...);
@@ -240,7 +243,7 @@ int group_launch_rows(int64_t max_rows, const int32_t *rows, int n_experts, int6
 // applies from two tiles per compute unit, counting the experts that may
 // have rows (below, the other forms' K splits keep more loads in flight).
 constexpr int64_t kSkinnyMaxRows = 64;
-bool skinny_down_fits(int64_t max_rows, int64_t active_experts, int N, int K);
+bool skinny_down_fits(int64_t max_rows, int64_t active_experts, int N);
 hipError_t launch_skinny_down(const moe_dims &d, int e_first, int e_count,
                               const int32_t *offsets, const bf16_t *act, const bf16_t *w_down,
                               float *y_perm, int64_t max_rows, int64_t active_experts,

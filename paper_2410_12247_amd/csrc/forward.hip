@@ -768,7 +768,7 @@ moe_status forward_impl(const moe_dims &d, const moe_opts &opt, const moe_bf16 *
                                                 w_up, act, grid, split_part, split_meta, bm, sr));
                 MOE_TRY(tm.end(sr));
                 MOE_TRY(tm.begin(sr, PH_DOWN));
-                if (skinny_down_fits(stage_max_rows, active, H, I))
+                if (skinny_down_fits(stage_max_rows, active, H))
                     MOE_HIP(launch_skinny_down(d, e_w, per_stage, goff, act, w_down, y_perm,
                                                stage_max_rows, active, sr));
                 else if (stream &&

@@ -975,17 +975,17 @@ __host__ __device__ constexpr int sk_ahead_max(int lps) {
     return SK_NS_MAX - 1 < 63 / lps ? SK_NS_MAX - 1 : 63 / lps;
 }
 // LDS-DMA requests per stage (64 lanes x 16 bytes each)
-__host__ __device__ constexpr int sk_lps(int bm, int bk) { return (SK_BN + bm) * bk * 2 / 1024; }
+__host__ __device__ constexpr int sk_lps(int bm) { return (SK_BN + bm) * SK_BK * 2 / 1024; }
 
-// LDS bytes of a workgroup with a ring of ns stages of bk K: the ring plus
+// LDS bytes of a workgroup with a ring of ns stages: the ring plus
 // room for the act-fragment reads a tile of fewer than 64 rows does not use
-__host__ __device__ constexpr size_t sk_lds_bytes(int bm, int bk, int ns) {
-    return (size_t)ns * (SK_BN + bm) * bk * 2 + (size_t)(4 - bm / 16) * 16 * bk * 2;
+__host__ __device__ constexpr size_t sk_lds_bytes(int bm, int ns) {
+    return (size_t)ns * (SK_BN + bm) * SK_BK * 2 + (size_t)(4 - bm / 16) * 16 * SK_BK * 2;
 }
 // stages of a tile of bm rows in `lds` bytes, as many as vmcnt can count
-__host__ __device__ constexpr int sk_ring(int bm, int bk, size_t lds) {
-    int ns = sk_ahead_max(sk_lps(bm, bk)) + 1;
-    while (ns > 1 && sk_lds_bytes(bm, bk, ns) > lds) --ns;
+__host__ __device__ constexpr int sk_ring(int bm, size_t lds) {
+    int ns = sk_ahead_max(sk_lps(bm)) + 1;
+    while (ns > 1 && sk_lds_bytes(bm, ns) > lds) --ns;
     return ns;
 }
 // LDS of a launch's workgroups: SK_LDS_MAX, two resident per compute unit;
@@ -993,7 +993,7 @@ __host__ __device__ constexpr int sk_ring(int bm, int bk, size_t lds) {
 // have rows is then resident at once.  us, two -> three: 700 tiles (2.7 per
 // unit) of 6144 x 1344 28.0 -> 26.4, of 6144 x 10752 176 -> 161; but 3.6 per
 // unit of 4096 x 6400 132 -> 160.
-constexpr size_t SK_LDS_THREE = sk_lds_bytes(32, 64, 4);
+constexpr size_t SK_LDS_THREE = sk_lds_bytes(32, 4);
 static_assert(3 * SK_LDS_THREE <= 160 * 1024, "three resident");
 
 // one K-step's fragments: 4 weight fragments from wa, 4 act fragments from
@@ -1028,20 +1028,19 @@ __device__ __forceinline__ void sk_wait(int n) {
 }
 
 // One tile: y columns n0 .. n0 + 63 of the `rows` <= BM rows from r0 on; w:
-// the expert's weights; ns ring stages of BK K.
-template <int BM, int BK>
+// the expert's weights; ns ring stages.
+template <int BM>
 __device__ __forceinline__ void skinny_tile(bf16_t *smem, int ns, int r0, int rows, int n0,
                                             const bf16_t *__restrict__ act,
                                             const bf16_t *__restrict__ w, int N, int K,
                                             float *__restrict__ y) {
-    constexpr int TN = SK_BN / 16, TM = BM / 16;
+    constexpr int TN = SK_BN / 16, TM = BM / 16, BK = SK_BK;
     static_assert(TM <= 4, "at most 4 act fragments per K-step");
-    static_assert(BK == 32 || BK == 64, "16-byte chunks: 4 or 8 per LDS row");
     constexpr int CPR = BK / 8;    // 16-byte chunks per LDS row
     constexpr int RPI = 64 / CPR;  // rows one LDS-DMA request fills
     constexpr int WI = SK_BN / RPI, XI = BM / RPI;
     constexpr int LPS = WI + XI;
-    static_assert(LPS == sk_lps(BM, BK), "requests per stage");
+    static_assert(LPS == sk_lps(BM), "requests per stage");
     constexpr int STAGE = (SK_BN + BM) * BK;  // bf16 elements
     constexpr int F = 16 * BK * 2;            // bytes of 16 LDS rows
     constexpr int KH = BK / 32;               // MFMA K-steps per stage
@@ -1130,7 +1129,7 @@ __device__ __forceinline__ void skinny_tile(bf16_t *smem, int ns, int r0, int ro
 // launch's bound, the tokens): against one height for the launch, us,
 // DeepSeekV2 61 tokens 62 -> 51, Zipf 64 tokens 20.5 -> 19.3, DBRX 64 tokens
 // 50.9 -> 49.0.
-template <int BK, size_t LDS>
+template <size_t LDS>
 __global__ __launch_bounds__(64) void skinny_down_kernel(const int32_t *__restrict__ offsets,
                                                          int e_first, int e_count,
                                                          const bf16_t *__restrict__ act,
@@ -1147,11 +1146,11 @@ __global__ __launch_bounds__(64) void skinny_down_kernel(const int32_t *__restri
     if (rows <= 0) return;  // (rows <= 64: the launcher's bound)
     const bf16_t *we = w + (int64_t)(e_first + e) * wstride;
     if (rows <= 16)
-        skinny_tile<16, BK>(smem, sk_ring(16, BK, LDS), r0, rows, n0, act, we, N, K, y);
+        skinny_tile<16>(smem, sk_ring(16, LDS), r0, rows, n0, act, we, N, K, y);
     else if (rows <= 32)
-        skinny_tile<32, BK>(smem, sk_ring(32, BK, LDS), r0, rows, n0, act, we, N, K, y);
+        skinny_tile<32>(smem, sk_ring(32, LDS), r0, rows, n0, act, we, N, K, y);
     else
-        skinny_tile<64, BK>(smem, sk_ring(64, BK, LDS), r0, rows, n0, act, we, N, K, y);
+        skinny_tile<64>(smem, sk_ring(64, LDS), r0, rows, n0, act, we, N, K, y);
 }
 
 int round_grid(int64_t tiles) { return (int)(((tiles + NXCD - 1) / NXCD) * NXCD); }
@@ -1244,7 +1243,12 @@ struct TileCost {
 // Fitted by least squares (4.0% rms gate/up, 4.5% down, 14% worst) to one
 // expert's dense launches at 512 .. 32768 rows on the DeepSeekV2 (H 5120,
 // I 1536) and Mixtral (H 4096, I 3584) expert shapes, every tile height,
-// with and without the K split (bench.py --tile-study).
+// with and without the K split (bench.py --tile-study), of tiles that ran
+// their epilogue after the K loop and branched in it.  On the present tiles
+// the same study reads 6.6% rms gate/up, 8.2% down, 18% worst (priced 4 and
+// 6% high on average); the height picked is the fastest at 24 of 27 points
+// and at most 5% off at the others.  Streaming and skinny launches are not
+// in the model.
 constexpr TileCost kTileCosts[] = {
     {320, {0.896, 1.004}, {13.0, 12.3}},
     {256, {0.750, 0.839}, {14.6, 12.8}},
@@ -1337,7 +1341,6 @@ int group_tile_rows(int64_t max_rows) {
     if (max_rows <= 128) return 128;
     if (max_rows <= 192) return 192;
     if (max_rows <= 256) return 256;
-    (void)max_rows;
     return kTokenTile;
 }
 
@@ -1463,8 +1466,8 @@ hipError_t launch_group_down(const moe_dims &d, int e_first, int e_count,
                               grid, parts, split_meta, (int)rows_one, s);
 }
 
-bool skinny_down_fits(int64_t max_rows, int64_t active_experts, int N, int K) {
-    return max_rows <= kSkinnyMaxRows && N % SK_BN == 0 && K % SK_BK == 0 &&
+bool skinny_down_fits(int64_t max_rows, int64_t active_experts, int N) {
+    return max_rows <= kSkinnyMaxRows &&
            active_experts * (N / SK_BN) >= 2 * (int64_t)device_cu_count();
 }
 
@@ -1474,16 +1477,17 @@ hipError_t launch_skinny_down(const moe_dims &d, int e_first, int e_count,
                               hipStream_t s) {
     if (e_count <= 0) return hipSuccess;
     const int N = d.hidden, K = d.inter;
-    if (N % SK_BN || K % SK_BK || max_rows > kSkinnyMaxRows) return hipErrorInvalidValue;
-    static_assert(sk_ring(64, SK_BK, SK_LDS_THREE) >= 2, "ring depth");
+    if (max_rows > kSkinnyMaxRows) return hipErrorInvalidValue;
+    static_assert(kDimAlign % SK_BN == 0 && kDimAlign % SK_BK == 0, "whole tiles and stages");
+    static_assert(sk_ring(64, SK_LDS_THREE) >= 2, "ring depth");
     const int64_t active = std::min<int64_t>(e_count, std::max<int64_t>(1, active_experts));
     const int64_t tiles = active * (N / SK_BN), cus = device_cu_count();
     const unsigned blocks = (unsigned)(e_count * (N / SK_BN));
     if (max_rows <= 32 && tiles > 2 * cus && tiles <= 3 * cus)
-        skinny_down_kernel<SK_BK, SK_LDS_THREE><<<blocks, 64, SK_LDS_THREE, s>>>(
+        skinny_down_kernel<SK_LDS_THREE><<<blocks, 64, SK_LDS_THREE, s>>>(
             offsets, e_first, e_count, act, w_down, (int64_t)N * K, N, K, y_perm);
     else
-        skinny_down_kernel<SK_BK, SK_LDS_MAX><<<blocks, 64, SK_LDS_MAX, s>>>(
+        skinny_down_kernel<SK_LDS_MAX><<<blocks, 64, SK_LDS_MAX, s>>>(
             offsets, e_first, e_count, act, w_down, (int64_t)N * K, N, K, y_perm);
     return hipGetLastError();
 }
