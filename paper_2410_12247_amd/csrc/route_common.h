@@ -93,6 +93,25 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
     return max(max(a, b), max(c, d));
 }
 
+// Lane j < k holds the j-th selected expert; those whose logit is the NaN of
+// all one bits (their rounds found no other) become the lowest experts not
+// taken, in order.
+__device__ __forceinline__ int repick_zero_keys(int my_e, float my_z, int E, int k, int lane) {
+    const uint64_t redo = __builtin_amdgcn_ballot_w64(lane < k && __float_as_uint(my_z) == ~0u);
+    for (int j = redo ? __builtin_ctzll(redo) : k; j < k; ++j) {
+        int e = 0;
+        for (int q = 3; q >= 0; --q) {
+            bool left = lane + 64 * q < E;
+            for (int p = 0; p < j; ++p)
+                left &= __builtin_amdgcn_readlane(my_e, p) != lane + 64 * q;
+            const uint64_t m = __builtin_amdgcn_ballot_w64(left);
+            if (m) e = 64 * q + __builtin_ctzll(m);
+        }
+        if (lane == j) my_e = e;
+    }
+    return my_e;
+}
+
 // Top-k and softmax weights of the N tokens t[i] (those below T) from their
 // E logits zrow[i], by one wave: lane l holds experts l, l+64, l+128, l+192;
 // each of the k rounds takes the wave-wide max of the logits'
@@ -102,7 +121,9 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
 // at once hide each other's cross-lane latency.  A token's k experts are
 // distinct whatever its logits (the row counts and buffers downstream rely
 // on it): bits of 0 mark a taken expert but are also those of the NaN of all
-// one bits, so once nothing above 0 is left the taken experts are compared.
+// one bits, so the rounds that found nothing above 0 are done again (after
+// the rounds, whose tokens a branch in them would keep apart: 65536 tokens x
+// 160 experts 798 -> 807 us).
 template <int N>
 __device__ __forceinline__ void select_tokens(const float *const (&zrow)[N],
                                               const int64_t (&t)[N], int64_t T, int E, int k,
@@ -112,10 +133,12 @@ __device__ __forceinline__ void select_tokens(const float *const (&zrow)[N],
     float zl[N][4];
     float my_z[N], zmax[N];
     int my_e[N];
+    uint32_t last[N];
 #pragma unroll
     for (int i = 0; i < N; ++i) {
         my_z[i] = zmax[i] = 0.0f;
         my_e[i] = 0;
+        last[i] = 1u;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int e = lane + 64 * q;
@@ -134,15 +157,6 @@ __device__ __forceinline__ void select_tokens(const float *const (&zrow)[N],
                 const uint64_t m = __builtin_amdgcn_ballot_w64(ord[i][q] == best);
                 if (m) e = 64 * q + __builtin_ctzll(m);
             }
-            if (best == 0u) {  // the lowest expert not taken
-                for (int q = 3; q >= 0; --q) {
-                    bool left = lane + 64 * q < E;
-                    for (int p = 0; p < j; ++p)
-                        left &= __builtin_amdgcn_readlane(my_e[i], p) != lane + 64 * q;
-                    const uint64_t m = __builtin_amdgcn_ballot_w64(left);
-                    if (m) e = 64 * q + __builtin_ctzll(m);
-                }
-            }
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 if (lane + 64 * q == e) ord[i][q] = 0u;
@@ -152,8 +166,12 @@ __device__ __forceinline__ void select_tokens(const float *const (&zrow)[N],
                 my_e[i] = e;
                 my_z[i] = z;
             }
+            last[i] = best;
         }
     }
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+        if (last[i] == 0u) my_e[i] = repick_zero_keys(my_e[i], my_z[i], E, k, lane);
     double ex[N], denom[N];
 #pragma unroll
     for (int i = 0; i < N; ++i) ex[i] = exp((double)my_z[i] - (double)zmax[i]);
