@@ -179,20 +179,20 @@ hipError_t launch(const int32_t *offsets, int e_first, int e_count, const bf16_t
 // of it resident at once, gains by the missing fix-up: up to 3 1/4 workgroups
 // per unit where a wave's piece of K is whole rounds of its steps in flight or
 // K is at most one round (4096 x 3584: 33 -> 28 at 448 workgroups, 46 -> 44 at
-// 740; 2048 x 1408: 29 -> 26 at 680), else up to 1 1/4 (5120 x 1536, whose 20
-// steps take the time of 24: 27 -> 23 at 200, 44 -> 48 at 580).  A larger one
-// gains while the tiled launch leaves units idle (6144 x 1344: 62% full 112 ->
-// 105, 94% 96 -> 86; 6144 x 2688, 98%: 61 -> 64), in whole rounds of K and,
-// where K is one round and a workgroup soon done, at most 16 of them per unit
-// (60 experts of 2048 x 1408, 21 per unit, 6 tokens 48 -> 57; 8 of 4096 x
-// 14336, 28 per unit, 6 tokens 328 -> 285).
+// 740; 2048 x 1408: 29 -> 26 at 680), else up to two (5120 x 1536, whose 20
+// steps take the time of 24: 27 -> 23 at 200, 37 -> 34 at 450, 59 -> 64 at
+// 800).  A larger one gains while the tiled launch leaves units idle (6144 x
+// 1344: 62% full 112 -> 105, 94% 96 -> 86; 6144 x 2688, 98%: 61 -> 64), in
+// whole rounds of K and, where K is one round and a workgroup soon done, at
+// most 16 of them per unit (60 experts of 2048 x 1408, 21 per unit, 6 tokens
+// 48 -> 57).
 bool stream_gateup_fits(int64_t max_rows, double active, int experts, int H, int I, int grid) {
     constexpr int ROUND = 32 * SW * kGateupSteps, MAX_H = 2 * ROUND;
     const double cus = device_cu_count();
     const double per_cu = experts * (I / 16) / cus, live = active * (I / 16) / cus;
     if (max_rows > kStreamMaxRows || per_cu > 32.0) return false;
     const bool whole = H % ROUND == 0;
-    if (live <= (H <= ROUND || (whole && H <= MAX_H) ? 3.25 : 1.25)) return true;
+    if (live <= (H <= ROUND || (whole && H <= MAX_H) ? 3.25 : 2.0)) return true;
     const int64_t tiles = std::llround(active * ((I + 127) / 128));
     return whole && (H > ROUND || per_cu <= 16.0) && tiled_round_fill(tiles, H, grid) < 0.95;
 }
