@@ -211,7 +211,10 @@ int32_t moe_workspace_guards(const moe_dims *dims, const moe_opts *opts, int64_t
  *                      over all E logits.
  * x [T][H] bf16; w_router [E][H] fp32; bias [E] fp32 or NULL;
  * topk_ids [T][k] int32 (global expert ids); topk_w [T][k] fp32.
- * Logits are never materialised.  NaN logits are not supported. */
+ * Logits are never materialised.  NaN logits are not supported (their weights
+ * are undefined; a token's k experts stay distinct).  x and w_router may sit at
+ * any address of their element type; x off 16 bytes takes slower kernels with
+ * the same bits. */
 moe_status moe_route(const moe_dims *dims, const moe_bf16 *x, const float *w_router,
                      const float *bias, int32_t *topk_ids, float *topk_w, void *stream);
 
